@@ -179,8 +179,8 @@ size_t redo_grape_workspace_bytes(redo_table table, int32_t B, int32_t N_max, in
 
 /* The smallest workspace redo_grape_fidelity_grad accepts for the same call
  * (Sec. III, GRAPE through REDO): at d <= 64 the checkpoints, one recomputed
- * segment and the pending traces, without the precomposed step propagators
- * (each scan step is then built from its factors); at d >= 128 the same as
+ * segment and the pending traces, without the step propagators and backward
+ * factors (each scan step is then built from its factors); at d >= 128 the same as
  * redo_grape_workspace_bytes.  The interval is part of the call: with 0 it is
  * the automatic one, at d <= 64 every state kept when that fits 8 GiB, so a
  * caller short of memory passes an explicit interval (ceil(sqrt(N_max)) gives
@@ -380,16 +380,16 @@ redo_status redo_unitary_fidelity(int32_t d, int32_t B, const float* U_target, c
  * segment the whole chain, written by the forward pass, so nothing is
  * recomputed (the same states, bit for bit), and 0 selects N_max when that
  * workspace (B N_max d^2 complex entries and the pending traces) is at most
- * 8 GiB, else ceil(sqrt(N_max)).  At
- * d <= 64, with the workspace that redo_workspace_bytes / redo_grape_workspace_bytes
- * report, every step's propagator U_n (B N_max d^2 complex entries, when that
- * is at most 4 GiB and the batch's threads, B (d/2)^2 below d = 64 and 256 B at
- * d = 64, are at most 65,536: batches too small to fill the GPU) is composed
- * first, all (instance, step) pairs in parallel, and each scan step is then one
- * product; a workspace of only the checkpoints,
- * one segment and the pending traces (the allocation-free entry's scratch) is
- * also accepted, and each scan step is then built from its factors (the same
- * result up to FP32 rounding).
+ * 8 GiB, else ceil(sqrt(N_max)).  At d = 8 .. 64 (d = 8: up to 4096 instances)
+ * the workspace that redo_workspace_bytes / redo_grape_workspace_bytes report
+ * holds every step's propagator, forward state and backward factor (3 B N_max d^2
+ * complex entries and 48 bytes per channel and step; at most 12 GiB, 4 GiB for an
+ * explicit interval, the batch then taken in parts): the propagators are composed
+ * first, all (instance, step) pairs in parallel, the two scans run at once, one
+ * product per step, and the traces of every step in parallel.  A workspace of only
+ * the checkpoints, one segment and the pending traces (the allocation-free entry's
+ * scratch) is also accepted, and each scan step is then built from its factors (the
+ * same result up to FP32 rounding).
  *   U_target  c64 [B][d][d];  fidelity double [B];  overlap c128 [B] or NULL
  *   grad      float, same layout as u (entries of steps >= n_steps[b] are set to 0)
  * Workspace: redo_workspace_bytes(table, REDO_OP_GRAPE, B, N_max).

@@ -735,8 +735,8 @@ size_t redo_workspace_bytes(redo_table t, int32_t op, int32_t B, int32_t N_max) 
             case REDO_OP_COMPOSE:
             case REDO_OP_CHAIN: return 0;
             case REDO_OP_GRAPE:
-                return small_grape_workspace_bytes(d, t->desc.K, B, N_max, small_grape_interval(t, B, N_max, 0)) +
-                       small_grape_precomposed_bytes(d, B, N_max);
+                return std::max(small_grape_workspace_bytes(d, t->desc.K, B, N_max, small_grape_interval(t, B, N_max, 0)),
+                                small_grape_scan_bytes(t, B, N_max, 0));
             default: return 0;
         }
     }
@@ -748,7 +748,8 @@ size_t redo_grape_workspace_bytes(redo_table t, int32_t B, int32_t N_max, int32_
     const int d = t->desc.d;
     if (small_dim(d)) {
         const long long C = small_grape_interval(t, B, N_max, checkpoint_every);
-        return small_grape_workspace_bytes(d, t->desc.K, B, N_max, C) + small_grape_precomposed_bytes(d, B, N_max);
+        return std::max(small_grape_workspace_bytes(d, t->desc.K, B, N_max, C),
+                        small_grape_scan_bytes(t, B, N_max, checkpoint_every));
     }
     return large_grape_workspace_bytes(t, B, N_max, checkpoint_every);
 }
@@ -1045,6 +1046,12 @@ redo_status redo_grape_fidelity_grad(redo_table t, int32_t precision, const floa
         const size_t need = small_grape_workspace_bytes(t->desc.d, t->desc.K, B, N_max, C);
         if (!workspace || workspace_bytes < need)
             return fail(REDO_ERR_WORKSPACE, "GRAPE workspace needs " + std::to_string(need) + " bytes");
+        // with room for every state and step propagator (redo_grape_workspace_bytes) both chains run
+        // at once and the traces in parallel; with less the fused form, checkpoints included
+        const size_t scan = small_grape_scan_bytes(t, B, N_max, checkpoint_every);
+        if (scan > 0 && workspace_bytes >= scan)
+            return small_grape_scan(t, u, n_steps, B, N_max, reinterpret_cast<const float2*>(U_target), checkpoint_every,
+                                    fidelity, reinterpret_cast<double2*>(overlap), grad, workspace, hs);
         SmallGrapeArgs a{};
         a.u = u;
         a.n_steps = n_steps;
@@ -1058,15 +1065,6 @@ redo_status redo_grape_fidelity_grad(redo_table t, int32_t precision, const floa
         a.n_ckpt = (int)nck;
         a.ckpt = static_cast<float2*>(workspace);
         a.seg = a.ckpt + (size_t)B * nck * t->desc.d * t->desc.d;
-        {
-            const size_t mats = sizeof(float2) * (size_t)t->desc.d * t->desc.d * (size_t)B * (size_t)(nck + C);
-            a.pend = reinterpret_cast<double*>(static_cast<char*>(workspace) + ((mats + 255) & ~size_t(255)));
-        }
-        // with room for every step's propagator, they are composed first (in parallel over steps) and
-        // each scan step is one product; with the minimum workspace each step is built from its factors
-        const size_t pre = small_grape_precomposed_bytes(t->desc.d, B, N_max);
-        if (pre > 0 && workspace_bytes >= need + pre)
-            a.Up = reinterpret_cast<float2*>(static_cast<char*>(workspace) + ((need + 255) & ~size_t(255)));
         REDO_HIP(small_grape(t, a, hs));
         return REDO_OK;
     }

@@ -90,8 +90,6 @@ redo_status redo_grape_fidelity_grad_noalloc(redo_table t, int32_t precision, co
     a.n_ckpt = (int)nck;
     a.ckpt = static_cast<float2*>(ws);
     a.seg = a.ckpt + (size_t)B * nck * d * d;
-    const size_t mats = sizeof(float2) * (size_t)d * d * (size_t)B * (size_t)(nck + C);
-    a.pend = reinterpret_cast<double*>(static_cast<char*>(ws) + ((mats + 255) & ~size_t(255)));
     REDO_HIP(small_grape(t, a, static_cast<hipStream_t>(stream)));
     return REDO_OK;
 }

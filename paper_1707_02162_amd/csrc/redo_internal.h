@@ -227,6 +227,8 @@ struct SmallChainArgs {
     const float2* obs_vals;
     int obs_width;
     double* obs_out;         // [B][N_max]
+    int drift0;              // instance b has drift (drift0 + b) % n_drift
+    int quiet;               // 1: another pass reports non-finite and clamped controls
 };
 hipError_t small_chain(const redo_table_s* t, const SmallChainArgs& a, hipStream_t st);
 
@@ -239,26 +241,29 @@ struct SmallGrapeArgs {
     double* fidelity;
     double2* overlap;
     float* grad;
-    float2* ckpt;            // workspace [B][n_ckpt][d][d]
-    float2* seg;             // workspace [B][checkpoint_every][d][d]
-    double* pend;            // workspace [B][K][6]: traces of the step whose gradient waits for the next D
+    float2* ckpt;            // workspace: n_ckpt states per instance
+    float2* seg;             // workspace: checkpoint_every states per instance
     int n_ckpt;
-    float2* Up;              // workspace [B][N_max][d][d]: the step propagators composed beforehand, or null
+    int drift0;              // instance b has drift (drift0 + b) % n_drift
 };
+// the fused form: one launch, every state or every checkpoint_every-th kept
 hipError_t small_grape(const redo_table_s* t, const SmallGrapeArgs& a, hipStream_t st);
-// workspace of the fused d <= 64 GRAPE kernel (checkpoints, one segment, pending traces)
 size_t small_grape_workspace_bytes(int d, int K, long long B, long long N_max, long long C);
-// the further workspace of the precomposed form (every step's U_n, 256-byte aligned start), 0 when
-// it would exceed SMALL_PRECOMPOSED_MAX, or when the batch's threads exceed
-// SMALL_PRECOMPOSED_MAX_THREADS (one wave per SIMD on 256 CUs); the fused form then builds
-// each step from its factors
-constexpr size_t SMALL_PRECOMPOSED_MAX = size_t(4) << 30;
-// the fused GRAPE (d <= 64) keeps every state of the forward pass (one checkpoint segment, no
-// recompute) when the checkpoint interval is left to the library and its workspace stays
-// within this; else it checkpoints every ceil(sqrt(N_max)) steps
+// the fused GRAPE keeps every state of the forward pass (one checkpoint segment, no recompute)
+// when the checkpoint interval is left to the library and its workspace stays within this;
+// else it checkpoints every ceil(sqrt(N_max)) steps
 constexpr size_t SMALL_FULL_STORAGE_MAX = size_t(8) << 30;
-constexpr long long SMALL_PRECOMPOSED_MAX_THREADS = 256LL * 4 * 64;
-size_t small_grape_precomposed_bytes(int d, long long B, long long N_max);
+// d = 8 .. 64 with room for it: both chains at once on stored states, then every trace in
+// parallel.  The batch is taken in parts that fit these limits (an explicit checkpoint interval
+// asks for less memory); requested: the call's checkpoint_every.  0: not one instance fits, the
+// fused form is used
+constexpr long long SMALL_SCAN_D8_BATCH = 4096;
+constexpr size_t SMALL_SCAN_MAX = size_t(12) << 30;
+constexpr size_t SMALL_SCAN_CHECKPOINTED_MAX = size_t(4) << 30;
+size_t small_grape_scan_bytes(const redo_table_s* t, long long B, long long N_max, long long requested);
+redo_status small_grape_scan(const redo_table_s* t, const float* u, const int* n_steps, int B, int N, const float2* U_target,
+                             long long requested, double* fidelity, double2* overlap, float* grad, void* workspace,
+                             hipStream_t st);
 
 // fidelity reduction, FP64
 hipError_t unitary_fidelity(int d, int B, const float2* Uf, const float2* U, double2* overlap,
