@@ -171,7 +171,7 @@ def bench_freezing(args, redo, W, torch):
                       if args.reproject > 0 else 0,
                       mag_last=m[:, -1].copy(), mag0=m[0].copy(), x0=U[0].cpu().numpy().astype(np.complex128))
         if kind == "kron":
-            # one launch per step reads and writes every realisation's state once (algorithmic bytes)
+            # every launch, of up to 16 steps, reads and writes every realisation's state once
             kbytes = 2.0 * 8 * p.d * p.d * B
             return dict(common, avg_launch_ms=kron_ms / max(kron_launches, 1), launches=kron_launches,
                         bytes_per_launch=kbytes,

@@ -20,6 +20,7 @@ struct redo_walsh_obs_s {
     float2* vals = nullptr;       // device [d][w]
     double* spec = nullptr;       // device [d]
     std::vector<double> spectrum; // host copy
+    std::vector<double> bits;     // f(2^q) when f has no other entries (a sum over single spins), else empty
 };
 
 namespace redo {
@@ -936,6 +937,19 @@ redo_status redo_walsh_observable_create(int32_t d, const int32_t* cols, const f
     h->d = d;
     h->w = width;
     h->spectrum = spec;
+    {
+        std::vector<double> bits(32, 0.0);
+        bool single = true;
+        for (int e = 0; e < width && single; ++e) {
+            const int c = cols[e];
+            if (vals[2 * e] == 0.f && vals[2 * e + 1] == 0.f) continue;
+            int q = 0;
+            while ((1 << q) < c) ++q;
+            single = c > 0 && (1 << q) == c && bits[q] == 0.0 && vals[2 * e + 1] == 0.f;   // no duplicates
+            if (single) bits[q] = vals[2 * e];
+        }
+        if (single) h->bits = bits;
+    }
     const size_t ne = (size_t)d * width;
     hipError_t e = hipMalloc((void**)&h->cols, sizeof(int) * ne);
     if (e == hipSuccess) e = hipMalloc((void**)&h->vals, sizeof(float2) * ne);
@@ -1014,7 +1028,7 @@ redo_status redo_kron_chain_walsh(redo_table t, int32_t quantised, const float* 
     return kron_chain(t, quantised, u, n_steps, B, N_max, step_offset, reproject_every, W0, W_total,
                       obs_out ? obs->cols : nullptr, obs_out ? reinterpret_cast<const float*>(obs->vals) : nullptr,
                       obs_out ? obs->w : 0, obs_out, workspace, workspace_bytes, static_cast<hipStream_t>(stream), true,
-                      obs_out ? obs->spec : nullptr);
+                      obs_out ? obs->spec : nullptr, obs_out && !obs->bits.empty() ? obs->bits.data() : nullptr);
 }
 
 redo_status redo_unitary_fidelity(int32_t d, int32_t B, const float* U_target, const float* U, double* overlap,

@@ -91,7 +91,9 @@ size_t kron_workspace_bytes(const redo_table_s* t, int B, int N);
 redo_status kron_chain(redo_table_s* t, int quantised, const float* u, const int* n_steps, int B, int N,
                        int step_offset, int reproject_every, const float* X0, float* U_total, const int* obs_cols,
                        const float* obs_vals, int obs_width, double* obs_out, void* workspace, size_t workspace_bytes,
-                       hipStream_t st, bool walsh_frame = false, const double* walsh = nullptr);
+                       hipStream_t st, bool walsh_frame = false, const double* walsh = nullptr,
+                       const double* bits = nullptr);
+// bits: host, the observable's entry f(2^q) per spin when it has no others, else null
 // walsh_frame: the state is carried in the right Walsh frame, W = X H / sqrt(d) (X0 and U_total
 // too; X0 = NULL starts from H / sqrt(d)), and the observable, M = Hn diag(walsh) Hn with walsh
 // its spectrum (device, d doubles), is evaluated there in one pass

@@ -214,3 +214,34 @@ def test_walsh_kron_d1024_fused_observable_with_reprojection_and_ragged():
     for b in range(3):
         nb = int(lens[b])
         assert np.abs(mw[b, :nb].cpu().numpy() - mk[b, :nb].cpu().numpy()).max() < OBS_TOL
+
+
+@pytest.mark.parametrize("n,B,N,every,quantised", [
+    (7, 3, 35, 0, False), (7, 2, 17, 16, True), (8, 3, 18, 5, False), (9, 2, 16, 1, False), (10, 3, 19, 7, False),
+    (10, 1, 1, 0, True)])
+@pytest.mark.parametrize("splitting", ["lie", "strang"])
+def test_walsh_kron_several_steps_per_launch_equal_single_steps(n, B, N, every, quantised, splitting):
+    """The chain of several steps per launch (a sum over single spins as the observable, or none)
+    against one launch per step (row lists): around the 16 steps of a launch, re-projections
+    inside, at the end of and right after one, ragged lengths, factors past a quarter turn."""
+    p = W.ising_freezing(n=n, B=B, N=N)
+    p.splitting = splitting
+    t = R().RedoTable.from_problem(p)
+    f = np.random.default_rng(n).normal(size=n).astype(np.float32)   # unequal weights
+    rows = np.arange(p.d)[:, None]
+    cols = (rows ^ (1 << np.arange(n))[None]).astype(np.int32)
+    vals = np.repeat(f[None], p.d, 0).astype(np.complex64)
+    D = R().walsh_observable(cols, vals)
+    u = torch.tensor(p.u).cuda()
+    if not quantised:   # spin factors by up to a full turn and more
+        u = u * (7.0 / (float(u.abs().max()) * p.dt))
+    lens = torch.tensor([N - (3 * b) % N for b in range(B)], dtype=torch.int32)
+    kw = dict(n_steps=lens, reproject_every=every, quantised=quantised)
+    Us, ms = t.kron_chain(u, observable=(cols, vals), **kw)
+    Uk, _ = t.kron_chain(u, **kw)
+    Wk, mk = t.kron_chain(u, walsh=D, **kw)
+    ref = Us.cpu().numpy().astype(np.complex128)
+    assert nfrob(Uk.cpu().numpy(), ref) < FROB_TOL and nfrob(to_x(Wk), ref) < FROB_TOL
+    for b in range(B):
+        nb = int(lens[b])
+        assert np.abs(mk[b, :nb].cpu().numpy() - ms[b, :nb].cpu().numpy()).max() < OBS_TOL
