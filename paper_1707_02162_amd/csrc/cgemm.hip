@@ -12,7 +12,7 @@
 // entry's tiles are scaled copies, done by the same launch.  FP32 complex
 // products use v_mfma_f32_32x32x2_f32 either as four real products (4M) or three
 // (Gauss, 3M); FP32 accumulation throughout (this file); split-BF16 products are
-// in cgemm_bf16.hip.
+// in cgemm_bf16.hip, split-FP16 products in cgemm_fp16.hip.
 // Tiles are staged through double-buffered LDS; tiles of one batch entry
 // are mapped to one XCD so its operands are shared in that XCD's L2.
 #include <cstdlib>
@@ -79,7 +79,7 @@ template <int BM, int BN, int MODE, int ROLE>
 // at least three waves per SIMD: the 3M form then keeps its 96 accumulators in VGPRs
 // (167 registers, no spills) instead of two waves with AGPRs, 240 -> 218 ms for 4096
 // products at d = 1024; the LDS already bounds every form at three workgroups per CU
-__global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int batch, const GemmDesc* __restrict__ descs) {
+__global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int only, const GemmDesc* __restrict__ descs) {
     using C = GCfg<BM, BN>;
     __shared__ float2 As[2][KT * C::LDA];
     __shared__ float2 Bs[2][KT * C::LDB];
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int batch, const G
     if (nb % NXCD == 0) bid = (bid % NXCD) * (nb / NXCD) + bid / NXCD;
     const int be = bid / ntile, tile = bid % ntile;
     const GemmDesc g = descs[be];
-    if (!g.active) return;
+    if (only ? g.active != only : !g.active) return;
     int i0, j0;
     if constexpr (GRAM) {
         gram_tile<BM, BN>(d, tile, i0, j0);
@@ -219,28 +219,28 @@ __global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int batch, const G
 }
 
 template <int BM, int BN, int MODE>
-hipError_t launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role) {
+hipError_t launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role, int only) {
     const long long tiles = role == GEMM_ROLE_GRAM ? gram_tile_count<BM, BN>(d) : (long long)(d / BM) * (d / BN);
     const long long blocks = tiles * batch;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     if (role == GEMM_ROLE_GRAM)
         hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, GEMM_ROLE_GRAM>), dim3((unsigned)blocks), dim3(256), 0, st, d,
-                           batch, descs);
+                           only, descs);
     else if (role == GEMM_ROLE_REPROJECT)
-        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 2>), dim3((unsigned)blocks), dim3(256), 0, st, d, batch, descs);
+        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 2>), dim3((unsigned)blocks), dim3(256), 0, st, d, only, descs);
     else if (role == GEMM_ROLE_COMPOSE)
-        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 3>), dim3((unsigned)blocks), dim3(256), 0, st, d, batch, descs);
+        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 3>), dim3((unsigned)blocks), dim3(256), 0, st, d, only, descs);
     else if (role == GEMM_ROLE_EXPM)
-        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 1>), dim3((unsigned)blocks), dim3(256), 0, st, d, batch, descs);
+        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 1>), dim3((unsigned)blocks), dim3(256), 0, st, d, only, descs);
     else
-        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 0>), dim3((unsigned)blocks), dim3(256), 0, st, d, batch, descs);
+        hipLaunchKernelGGL((cgemm_kernel<BM, BN, MODE, 0>), dim3((unsigned)blocks), dim3(256), 0, st, d, only, descs);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// precision: 0 = 4M FP32, 1 = 3M FP32, 2 = split BF16 (hi*hi + hi*lo + lo*hi)
-hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision, hipStream_t st, int role) {
+// precision: 0 = 4M FP32, 1 = 3M FP32, 2 = split BF16 (hi*hi + hi*lo + lo*hi), GEMM_FP16*: split FP16
+hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision, hipStream_t st, int role, int only) {
     if (d % 64 != 0 || batch < 1) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     const bool big = d % 128 == 0 && (long long)(d / 128) * (d / 64) * batch >= 512;
@@ -249,12 +249,14 @@ hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision,
     if (prof) profile_begin(st, &tok, role == GEMM_ROLE_REPROJECT || role == GEMM_ROLE_GRAM ? 2 : 0);
     // 128x64 tiles: three workgroups per CU for 4M (64 accumulator registers per lane); 3M (96)
     // is also faster there than on 128x128 tiles (240 vs 280 ms for 4096 products at d = 1024)
-    if (precision == 2)
+    if (precision >= GEMM_FP16)
+        e = cgemm_fp16_launch(d, batch, descs, st, role, big, precision == GEMM_FP16_EXACT_A);
+    else if (precision == 2)
         e = cgemm_bf16_launch(d, batch, descs, st, role, big);
     else if (precision == 1)
-        e = big ? launch<128, 64, 1>(d, batch, descs, st, role) : launch<64, 64, 1>(d, batch, descs, st, role);
+        e = big ? launch<128, 64, 1>(d, batch, descs, st, role, only) : launch<64, 64, 1>(d, batch, descs, st, role, only);
     else
-        e = big ? launch<128, 64, 0>(d, batch, descs, st, role) : launch<64, 64, 0>(d, batch, descs, st, role);
+        e = big ? launch<128, 64, 0>(d, batch, descs, st, role, only) : launch<64, 64, 0>(d, batch, descs, st, role, only);
     if (prof) profile_end(st, tok);
     return e;
 }

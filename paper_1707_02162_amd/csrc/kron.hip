@@ -675,6 +675,7 @@ struct KronWS {
     float2* E;   // re-projection scratch: E = (I - X^dag X) / 2 of a chunk
     double* obs_partial;
     int* loc;
+    int* plain;
     float2* obsT;
     int chunk;               // steps per launch (kron_multi), else 1
     float* rot;              // [B][chunk][16] rotations (kron_multi)
@@ -698,6 +699,7 @@ struct KronWS {
         E = c.take<float2>(mat * std::min(B, REPROJECT_CHUNK));
         obs_partial = c.take<double>(observable_partial_doubles(d, B));
         loc = c.take<int>(B);
+        plain = c.take<int>(B);
         obsT = c.take<float2>(mat * std::min(B, OBS_CHUNK));
         bytes = c.used;
     }
@@ -728,6 +730,8 @@ redo_status kron_chain(redo_table_s* t, int quantised, const float* u, const int
         REDO_HIP(walsh_frame ? walsh_fill(d, B, X[0], mat, st) : fill_identity(d, B, X[0], mat, st));
     else if (X0 != U_total)
         REDO_HIP(hipMemcpyAsync(X[0], X0, sizeof(float2) * mat * B, hipMemcpyDeviceToDevice, st));
+    StepProducts gram{1, 1, nullptr};
+    if (reproject_every > 0) REDO_HIP(chain_products(d, B, 1, false, X[0], X0 != nullptr, mat, w.plain, &gram, st));
     REDO_HIP(fill_int(w.loc, B, 0, st));
     KronPlanArgs pa{};
     pa.s = t->kron_s;
@@ -809,8 +813,8 @@ redo_status kron_chain(redo_table_s* t, int quantised, const float* u, const int
                                    n_steps, n, obs_out + n, (long long)N);
                 REDO_HIP(hipGetLastError());
             }
-            if (reproj) {   // X <- X (3I - X^dag X) / 2 into the other buffer, Gram product in 3M FP32
-                REDO_HIP(reproject_states(d, B, X[0], X[1], mat, w.E, w.descs, w.loc, n_steps, n + T - 1, 1, t->flags, st));
+            if (reproj) {   // X <- X (3I - X^dag X) / 2 into the other buffer
+                REDO_HIP(reproject_states(d, B, X[0], X[1], mat, w.E, w.descs, w.loc, n_steps, n + T - 1, gram, t->flags, st));
                 if (ob)
                     REDO_HIP(observable_walsh(d, B, X[0], X[1], w.loc, mat, obs_cols, reinterpret_cast<const float2*>(obs_vals),
                                               obs_width, walsh, n_steps, n + T - 1, w.obs_partial, obs_out + n + T - 1, N, st));
@@ -832,8 +836,8 @@ redo_status kron_chain(redo_table_s* t, int quantised, const float* u, const int
             continue;
         }
         REDO_HIP(kron_step(d, B, X[0], X[1], w.loc, mat, w.gates, w.pre, w.post, n_steps, n, st));
-        if (reproj)   // X <- X (3I - X^dag X) / 2 into the other buffer, Gram product in 3M FP32
-            REDO_HIP(reproject_states(d, B, X[0], X[1], mat, w.E, w.descs, w.loc, n_steps, n, 1, t->flags, st));
+        if (reproj)   // X <- X (3I - X^dag X) / 2 into the other buffer
+            REDO_HIP(reproject_states(d, B, X[0], X[1], mat, w.E, w.descs, w.loc, n_steps, n, gram, t->flags, st));
         if (obs_out)
             REDO_HIP(walsh_frame ? observable_walsh(d, B, X[0], X[1], w.loc, mat, obs_cols,
                                              reinterpret_cast<const float2*>(obs_vals), obs_width, walsh, n_steps,

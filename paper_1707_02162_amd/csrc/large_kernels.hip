@@ -31,6 +31,7 @@ struct PlanArgs {
     float2* X[2];           // state buffers (per instance stride xstride)
     long long xstride;
     int* loc;               // [B]: which buffer holds the state of instance b (updated here)
+    const int* plain;       // [B]: 1 = no split-FP16 products for this instance, or null
     int compose;            // 1: the state starts as the identity (no B operand)
     int slots;              // launched slots: dense + K (all levels cached) or dense + K * P
     int all_cached;
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(256) void plan_step_kernel(PlanArgs a) {
         GemmDesc g{};
         g.alpha = 1.f;
         const bool use = fa[s] != nullptr || s == copy_slot;
-        g.active = use ? 1 : 0;
+        g.active = use ? (a.plain && a.plain[b] ? 2 : 1) : 0;
         if (use) {
             g.A = fa[s];
             g.opA = fo[s];
@@ -142,7 +143,8 @@ __global__ __launch_bounds__(256) void plan_step_kernel(PlanArgs a) {
 // phase 0: E_b = (I - X^dag X) / 2 (a Gram product);  phase 1: X'_b = X_b + X_b E_b into the
 // other buffer (and flip loc)
 __global__ void reproject_descs_kernel(GemmDesc* descs, int count, int b0, float2* X0, float2* X1, long long xstride,
-                                       float2* E, long long estride, int* loc, const int* n_steps, int step, int phase) {
+                                       float2* E, long long estride, int* loc, const int* plain, const int* n_steps,
+                                       int step, int phase) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
     const int b = b0 + i;
@@ -153,6 +155,7 @@ __global__ void reproject_descs_kernel(GemmDesc* descs, int count, int b0, float
     const int l = loc[b];
     float2* xb = X[l] + (long long)b * xstride;
     if (phase == 0) {
+        if (active && plain && plain[b]) g.active = 2;
         g.A = xb;
         g.opA = 1;
         g.B = xb;
@@ -192,6 +195,26 @@ __global__ __launch_bounds__(256) void unitarity_check_kernel(int d, const float
         __syncthreads();
     }
     if (threadIdx.x == 0) report_drift(flags, 2.0 * sqrt(part[0] / d));
+}
+
+// plain[b] = 1 where a column of the state is neither zero nor of a norm in [1/2, 2] (or not
+// finite): such a state's products stay in FP32.  64 columns per workgroup
+__global__ __launch_bounds__(256) void state_columns_kernel(int d, const float2* __restrict__ X, long long xstride,
+                                                            int* plain) {
+    const int b = blockIdx.y, c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+    const float2* x = X + (long long)b * xstride + blockIdx.x * 64 + c;
+    float s = 0.f;
+    for (int r = r0; r < d; r += 4) {
+        const float2 v = x[(long long)r * d];
+        s = fmaf(v.x, v.x, fmaf(v.y, v.y, s));
+    }
+    __shared__ float part[4][64];
+    part[r0][c] = s;
+    __syncthreads();
+    if (r0 == 0) {
+        s += part[1][c] + part[2][c] + part[3][c];
+        if (!(s == 0.f || (s >= 0.25f && s <= 4.f))) plain[b] = 1;
+    }
 }
 
 // copies the states that ended in buffer 1 back to buffer 0
@@ -1332,6 +1355,7 @@ hipError_t plan_step(const PlanLaunch& p, hipStream_t st) {
     a.X[1] = p.X1;
     a.xstride = p.xstride;
     a.loc = p.loc;
+    a.plain = p.plain;
     a.compose = p.compose;
     a.slots = p.slots;
     a.all_cached = p.all_cached;
@@ -1348,9 +1372,10 @@ hipError_t plan_step(const PlanLaunch& p, hipStream_t st) {
 }
 
 hipError_t reproject_descs(GemmDesc* descs, int count, int b0, float2* X0, float2* X1, long long xstride, float2* E,
-                           long long estride, int* loc, const int* n_steps, int step, int phase, hipStream_t st) {
+                           long long estride, int* loc, const int* plain, const int* n_steps, int step, int phase,
+                           hipStream_t st) {
     hipLaunchKernelGGL(reproject_descs_kernel, dim3((count + 63) / 64), dim3(64), 0, st, descs, count, b0, X0, X1,
-                       xstride, E, estride, loc, n_steps, step, phase);
+                       xstride, E, estride, loc, plain, n_steps, step, phase);
     return hipGetLastError();
 }
 
@@ -1361,17 +1386,24 @@ hipError_t unitarity_check(int d, int count, int b0, const float2* E, long long 
 }
 
 hipError_t reproject_states(int d, int B, float2* X0, float2* X1, long long xstride, float2* E, GemmDesc* descs,
-                            int* loc, const int* n_steps, int step, int precision, DeviceFlags* flags, hipStream_t st) {
+                            int* loc, const int* n_steps, int step, StepProducts gram, DeviceFlags* flags, hipStream_t st) {
     for (int b0 = 0; b0 < B; b0 += REPROJECT_CHUNK) {
         const int ch = std::min(REPROJECT_CHUNK, B - b0);
-        hipError_t e = reproject_descs(descs, ch, b0, X0, X1, xstride, E, xstride, loc, n_steps, step, 0, st);
-        if (e == hipSuccess) e = cgemm_batched(d, ch, descs, precision, st, GEMM_ROLE_GRAM);
+        hipError_t e = reproject_descs(descs, ch, b0, X0, X1, xstride, E, xstride, loc, gram.plain, n_steps, step, 0, st);
+        if (e == hipSuccess) e = gram.run(d, ch, descs, st, GEMM_ROLE_GRAM);
         if (e == hipSuccess) e = unitarity_check(d, ch, b0, E, xstride, n_steps, step, flags, st);
-        if (e == hipSuccess) e = reproject_descs(descs, ch, b0, X0, X1, xstride, E, xstride, loc, n_steps, step, 1, st);
+        if (e == hipSuccess) e = reproject_descs(descs, ch, b0, X0, X1, xstride, E, xstride, loc, gram.plain, n_steps, step, 1, st);
         if (e == hipSuccess) e = cgemm_batched(d, ch, descs, 2, st, GEMM_ROLE_REPROJECT);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t state_columns(int d, int B, const float2* X, long long xstride, int* plain, hipStream_t st) {
+    const hipError_t e = fill_int(plain, B, 0, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(state_columns_kernel, dim3(d / 64, B), dim3(256), 0, st, d, X, xstride, plain);
+    return hipGetLastError();
 }
 
 hipError_t gather_back(int d, int B, float2* X0, const float2* X1, long long xstride, const int* loc, hipStream_t st) {

@@ -39,6 +39,7 @@ struct ChainWS {
     float2* E;   // re-projection scratch: E = (I - X^dag X) / 2 of a chunk
     double* obs_partial;
     int* loc;
+    int* plain;
     float2* obsT;
     size_t bytes;
     ChainWS(const redo_table_s* t, int B, int N, void* base) {
@@ -55,6 +56,7 @@ struct ChainWS {
         E = c.take<float2>(mat * std::min(B, REPROJECT_CHUNK));
         obs_partial = c.take<double>(observable_partial_doubles(d, B));
         loc = c.take<int>(B);
+        plain = c.take<int>(B);
         obsT = c.take<float2>(mat * std::min(B, OBS_CHUNK));
         bytes = c.used;
     }
@@ -255,6 +257,13 @@ redo_status compose_pairs(redo_table_s* t, int precision, long long I, int N, co
 
 }  // namespace
 
+hipError_t chain_products(int d, int B, int fp32, bool exact_a, const float2* X, bool given, long long xstride,
+                          int* plain, StepProducts* out, hipStream_t st) {
+    const bool split = fp32 < 2 && d >= 192;
+    *out = StepProducts{split ? (exact_a ? GEMM_FP16_EXACT_A : GEMM_FP16) : fp32, fp32, split && given ? plain : nullptr};
+    return out->plain ? state_columns(d, B, X, xstride, plain, st) : hipSuccess;
+}
+
 size_t large_workspace_bytes(const redo_table_s* t, int op, int B, int N) {
     switch (op) {
         case REDO_OP_COMPOSE: return ComposeWS(t, (long long)B * N, nullptr).bytes;
@@ -315,7 +324,8 @@ redo_status large_chain(redo_table_s* t, int precision, const float* u, const in
         REDO_HIP(hipMemcpyAsync(X[0], X0, sizeof(float2) * mat * B, hipMemcpyDeviceToDevice, st));
     REDO_HIP(fill_int(w.loc, B, 0, st));
     const int S = launch_slots(t);
-    const int prec = gemm_prec(precision);
+    StepProducts prod;
+    REDO_HIP(chain_products(d, B, gemm_prec(precision), !all_cached(t), X[0], X0 != nullptr, mat, w.plain, &prod, st));
     for (int n = 0; n < N; ++n) {
         PlanLaunch p = plan_base(t);
         p.codes = w.codes + (size_t)n * t->desc.K;
@@ -326,15 +336,16 @@ redo_status large_chain(redo_table_s* t, int precision, const float* u, const in
         p.X0 = X[0];
         p.X1 = X[1];
         p.loc = w.loc;
+        p.plain = prod.plain;
         p.pre = w.pre;
         p.post = w.post;
         p.pstar = w.pstar;
         p.descs = w.descs;
         p.B = B;
         REDO_HIP(plan_step(p, st));
-        for (int sl = 0; sl < S; ++sl) REDO_HIP(cgemm_batched(d, B, w.descs + (size_t)sl * B, prec, st));
+        for (int sl = 0; sl < S; ++sl) REDO_HIP(prod.run(d, B, w.descs + (size_t)sl * B, st, GEMM_ROLE_STEP));
         if (reproject_every > 0 && ((long long)step_offset + n + 1) % reproject_every == 0)
-            REDO_HIP(reproject_states(d, B, X[0], X[1], mat, w.E, w.descs, w.loc, n_steps, n, prec, t->flags, st));
+            REDO_HIP(reproject_states(d, B, X[0], X[1], mat, w.E, w.descs, w.loc, n_steps, n, prod, t->flags, st));
         if (obs_out)
             REDO_HIP(walsh_frame ? observable_walsh(d, B, X[0], X[1], w.loc, mat, obs_cols,
                                              reinterpret_cast<const float2*>(obs_vals), obs_width, walsh, n_steps,

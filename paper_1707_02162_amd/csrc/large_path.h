@@ -49,6 +49,7 @@ struct PlanLaunch {
     float2* X1;
     long long xstride;
     int* loc;
+    const int* plain;        // split FP16: the instances that stay in FP32, or null
     int compose, slots, all_cached;
     const uint16_t* cache_bf;   // pre-split BF16 panels of the cache (split-BF16 products), or null
     int bf_conj;             // negative levels take the conjugated panel of |q|
@@ -60,6 +61,24 @@ struct PlanLaunch {
     int B;
 };
 hipError_t plan_step(const PlanLaunch& p, hipStream_t st);
+
+// The products of a chain's steps.  FP32 chains from d = 192 take split FP16, whose errors are no
+// larger there (cgemm_fp16.hip): factors are unitary, and so is a state that starts as the
+// identity.  A start given by the caller is looked at first (state_columns), and instances whose
+// columns are not near unit norm take the FP32 products of the call's precision, in a second launch
+// that leaves the others out.
+struct StepProducts {
+    int prec, fp32;
+    const int* plain;   // [B] or null: no such instances
+    hipError_t run(int d, int batch, const GemmDesc* descs, hipStream_t st, int role) const {
+        const hipError_t e = cgemm_batched(d, batch, descs, prec, st, role);
+        return e == hipSuccess && plain ? cgemm_batched(d, batch, descs, fp32, st, role, 2) : e;
+    }
+};
+// fp32: 0 (4M), 1 (3M) or 2 (split BF16, kept); exact_a: digit operators among the factors; plain:
+// B ints of scratch, filled from the states X if the caller gave them
+hipError_t chain_products(int d, int B, int fp32, bool exact_a, const float2* X, bool given, long long xstride,
+                          int* plain, StepProducts* out, hipStream_t st);
 
 // inactive_mode: 0 skip the entry, 1 copy op(B) into C, 2 copy op(A) into C
 hipError_t fill_descs(GemmDesc* descs, int count, const float2* A, long long sA, int opA, const float2* B,
@@ -158,16 +177,18 @@ hipError_t observable_walsh(int d, int B, const float2* X0, const float2* X1, co
 hipError_t unitarity_check(int d, int count, int b0, const float2* E, long long estride, const int* n_steps, int step,
                            DeviceFlags* flags, hipStream_t st);
 hipError_t reproject_descs(GemmDesc* descs, int count, int b0, float2* X0, float2* X1, long long xstride, float2* E,
-                           long long estride, int* loc, const int* n_steps, int step, int phase, hipStream_t st);
+                           long long estride, int* loc, const int* plain, const int* n_steps, int step, int phase,
+                           hipStream_t st);
 // Newton-Schulz re-projection of every active instance at a re-projection step,
 // X <- X (3I - X^dag X) / 2 written as X + X E with E = (I - X^dag X) / 2, REPROJECT_CHUNK
 // instances at a time through the scratch E (xstride apart) and descs (REPROJECT_CHUNK
-// entries): the Gram product X^dag X at the given GEMM precision (Hermitian: the upper tiles
+// entries): the Gram product X^dag X in the form of the chain's own products (Hermitian: the upper tiles
 // only), the unitarity watchdog on E, then X E as a split-BF16 product with X added in FP32
 // into the other buffer (loc flips).  E is of the order of the drift, so the split's relative
 // error of about 2^-16 in X E stays far below the FP32 rounding of X itself.
 hipError_t reproject_states(int d, int B, float2* X0, float2* X1, long long xstride, float2* E, GemmDesc* descs,
-                            int* loc, const int* n_steps, int step, int precision, DeviceFlags* flags, hipStream_t st);
+                            int* loc, const int* n_steps, int step, StepProducts gram, DeviceFlags* flags, hipStream_t st);
+hipError_t state_columns(int d, int B, const float2* X, long long xstride, int* plain, hipStream_t st);
 hipError_t gather_back(int d, int B, float2* X0, const float2* X1, long long xstride, const int* loc, hipStream_t st);
 hipError_t fill_int(int* p, int n, int v, hipStream_t st);
 size_t trace_partial_doubles(int d, int B, int K);

@@ -286,7 +286,7 @@ struct GemmDesc {
     const float2* cscale;  // scales column j of C, or null
     int opA;             // 0: A, 1: A^H
     int opB;             // 0: B, 1: B^H
-    int active;          // 0: skip this entry entirely
+    int active;          // 0: skip this entry entirely; 2: not for split FP16 (a state off unit columns)
     float beta_identity; // C += beta * I after scaling (Newton-Schulz), usually 0
     float alpha;         // C = alpha * (...)
     int conjA;           // with Abf: op(A) = conj(panel matrix), which equals its adjoint (symmetric)
@@ -306,9 +306,14 @@ static_assert(sizeof(GemmDesc) % 8 == 0, "desc alignment");
 // diagonal.  Re-projection launches (roles 2 and 4) are timed as profile kind 2
 constexpr int GEMM_ROLE_STEP = 0, GEMM_ROLE_EXPM = 1, GEMM_ROLE_REPROJECT = 2, GEMM_ROLE_COMPOSE = 3,
               GEMM_ROLE_GRAM = 4;
-hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision, hipStream_t st, int role = 0);
+// only: FP32 products of the entries with this `active` alone (0: of every active one); split FP16
+// runs those with active == 1
+constexpr int GEMM_FP16 = 3, GEMM_FP16_EXACT_A = 4;
+hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision, hipStream_t st, int role = 0, int only = 0);
 // the split-BF16 launch behind cgemm_batched (cgemm_bf16.hip): 128 x 64 tiles when big, else 64 x 64
 hipError_t cgemm_bf16_launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role, bool big);
+// the split-FP16 launch (cgemm_fp16.hip); exact_a: every bit of A, where the sums are short
+hipError_t cgemm_fp16_launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role, bool big, bool exact_a);
 
 // launch timing (profile.cpp)
 bool profiling_on();
