@@ -437,6 +437,48 @@ redo_status redo_build_table(const redo_table_desc* desc, const double* H0, cons
         }
     }
 
+    // a diagonal gauge D = diag(i^c) in which every generator is imaginary, so that every factor
+    // exp(-i theta S_k) = D Q D^* with Q real: no diagonal, real entries between rows of different
+    // colour c, imaginary ones between rows of one colour (collective and single-spin x or y drives)
+    if (large_dim(d) && desc->drift_is_diag) {
+        std::vector<signed char> c(d, -1);
+        std::vector<int> queue;
+        bool ok = true;
+        for (int s0 = 0; s0 < d && ok; ++s0) {
+            if (c[s0] >= 0) continue;
+            c[s0] = 0;
+            queue.assign(1, s0);
+            for (size_t h = 0; h < queue.size() && ok; ++h) {
+                const int i = queue[h];
+                for (int k = 0; k < K && ok; ++k) {
+                    const double* row = hS.data() + 2 * (nn * k + (size_t)i * d);
+                    for (int j = 0; j < d && ok; ++j) {
+                        const double re = row[2 * j], im = row[2 * j + 1];
+                        if (re == 0.0 && im == 0.0) continue;
+                        if (j == i || (re != 0.0 && im != 0.0)) {
+                            ok = false;
+                            continue;
+                        }
+                        const signed char want = c[i] ^ (im == 0.0 ? 1 : 0);
+                        if (c[j] < 0) {
+                            c[j] = want;
+                            queue.push_back(j);
+                        } else if (c[j] != want) {
+                            ok = false;
+                        }
+                    }
+                }
+            }
+        }
+        if (ok) {
+            std::vector<unsigned> masks(d);
+            for (int i = 0; i < d; ++i) masks[i] = c[i] ? 0xffffffffu : 0u;
+            REDO_HIP(alloc((void**)&t->colour, sizeof(unsigned) * masks.size()));
+            REDO_HIP(hipMemcpyAsync(t->colour, masks.data(), sizeof(unsigned) * masks.size(), hipMemcpyHostToDevice, hs));
+            REDO_HIP(hipStreamSynchronize(hs));
+        }
+    }
+
     // ---- FP64 build: E_kj = exp(-i b^j eps dt S_k), T_kj[c] = E_kj^c (powers by doubling)
     {
         DevBuf E, Tj, scratch;
@@ -527,7 +569,8 @@ redo_status redo_table_destroy(redo_table t) {
     if (!t) return REDO_OK;
     (void)hipDeviceSynchronize();
     void* bufs[] = {t->T32,   t->h64,    t->V32,       t->g64,       t->g2,     t->S32,    t->S64,   t->Sy32,
-                    t->H32,   t->flags,  t->cache,     t->cache_bf,  t->spat_cols, t->spat_vals, t->kron_s};
+                    t->H32,   t->flags,  t->cache,     t->cache_bf,  t->spat_cols, t->spat_vals, t->kron_s,
+                    t->colour};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     delete t;

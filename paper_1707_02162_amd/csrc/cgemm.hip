@@ -12,7 +12,7 @@
 // entry's tiles are scaled copies, done by the same launch.  FP32 complex
 // products use v_mfma_f32_32x32x2_f32 either as four real products (4M) or three
 // (Gauss, 3M); FP32 accumulation throughout (this file); split-BF16 products are
-// in cgemm_bf16.hip, split-FP16 products in cgemm_fp16.hip.
+// in cgemm_bf16.hip, split-FP16 products in cgemm_split.hip.
 // Tiles are staged through double-buffered LDS; tiles of one batch entry
 // are mapped to one XCD so its operands are shared in that XCD's L2.
 #include <cstdlib>
@@ -243,14 +243,18 @@ hipError_t launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int r
 hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision, hipStream_t st, int role, int only) {
     if (d % 64 != 0 || batch < 1) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
-    const bool big = d % 128 == 0 && (long long)(d / 128) * (d / 64) * batch >= 512;
+    const bool big = cgemm_big(d, batch);
     void* tok = nullptr;
     const bool prof = profiling_on();
     if (prof) profile_begin(st, &tok, role == GEMM_ROLE_REPROJECT || role == GEMM_ROLE_GRAM ? 2 : 0);
     // 128x64 tiles: three workgroups per CU for 4M (64 accumulator registers per lane); 3M (96)
     // is also faster there than on 128x128 tiles (240 vs 280 ms for 4096 products at d = 1024)
+    const bool real = (precision & GEMM_REAL) != 0;
+    precision &= ~GEMM_REAL;
     if (precision >= GEMM_FP16)
-        e = cgemm_fp16_launch(d, batch, descs, st, role, big, precision == GEMM_FP16_EXACT_A);
+        e = cgemm_fp16_launch(d, batch, descs, st, role, big, precision == GEMM_FP16_EXACT_A, real);
+    else if (precision == 2 && real && role == GEMM_ROLE_STEP)
+        e = cgemm_bf16_real_launch(d, batch, descs, st);
     else if (precision == 2)
         e = cgemm_bf16_launch(d, batch, descs, st, role, big);
     else if (precision == 1)

@@ -730,8 +730,8 @@ redo_status kron_chain(redo_table_s* t, int quantised, const float* u, const int
         REDO_HIP(walsh_frame ? walsh_fill(d, B, X[0], mat, st) : fill_identity(d, B, X[0], mat, st));
     else if (X0 != U_total)
         REDO_HIP(hipMemcpyAsync(X[0], X0, sizeof(float2) * mat * B, hipMemcpyDeviceToDevice, st));
-    StepProducts gram{1, 1, nullptr};
-    if (reproject_every > 0) REDO_HIP(chain_products(d, B, 1, false, X[0], X0 != nullptr, mat, w.plain, &gram, st));
+    StepProducts gram{1, 1, nullptr, nullptr};
+    if (reproject_every > 0) REDO_HIP(chain_products(t, B, 1, X[0], X0 != nullptr, w.plain, &gram, st));
     REDO_HIP(fill_int(w.loc, B, 0, st));
     KronPlanArgs pa{};
     pa.s = t->kron_s;

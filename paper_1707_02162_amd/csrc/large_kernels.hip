@@ -31,6 +31,7 @@ struct PlanArgs {
     float2* X[2];           // state buffers (per instance stride xstride)
     long long xstride;
     int* loc;               // [B]: which buffer holds the state of instance b (updated here)
+    const unsigned* colour; // gauge of the factors (GemmDesc::colour), or null
     const int* plain;       // [B]: 1 = no split-FP16 products for this instance, or null
     int compose;            // 1: the state starts as the identity (no B operand)
     int slots;              // launched slots: dense + K (all levels cached) or dense + K * P
@@ -57,6 +58,9 @@ __global__ __launch_bounds__(256) void plan_step_kernel(PlanArgs a) {
     const int* cb = a.codes + (long long)b * a.code_stride;
     const double* pb = a.phi ? a.phi + (long long)b * a.code_stride : nullptr;
     const int drift = (int)(((a.drift_offset + b) / a.drift_div) % a.n_drift);
+    // D^* of the gauge goes into the scaling before the factors, D into the one after them (exact)
+    const bool plain = a.plain && a.plain[b];
+    const unsigned* colour = plain ? nullptr : a.colour;
     if (active)
         for (int r = threadIdx.x; r < d; r += blockDim.x) {
             double th = 0.0;
@@ -64,12 +68,13 @@ __global__ __launch_bounds__(256) void plan_step_kernel(PlanArgs a) {
                 for (int k = 0; k < a.K; ++k) th += pb[k] * a.g[(long long)k * d + r];
             const double hd = (!a.dense && a.strang) ? 0.5 * a.dt * a.h[(long long)drift * d + r] : 0.0;
             const double2 po = expmi(th + hd);                   // e^{-i theta} (times v^{1/2}, Strang)
-            a.post[(long long)b * d + r] = make_float2((float)po.x, (float)po.y);
+            const bool turn = colour && colour[r] != 0;
+            a.post[(long long)b * d + r] = turn ? make_float2((float)-po.y, (float)po.x) : make_float2((float)po.x, (float)po.y);
             a.pstar[(long long)b * d + r] = make_float2((float)po.x, (float)-po.y);
             if (!a.dense) {
                 const double hdt = a.strang ? 0.5 * a.dt : a.dt;
                 const double2 pr = expmi(hdt * a.h[(long long)drift * d + r] - th);   // v e^{+i theta}
-                a.pre[(long long)b * d + r] = make_float2((float)pr.x, (float)pr.y);
+                a.pre[(long long)b * d + r] = turn ? make_float2((float)pr.y, (float)-pr.x) : make_float2((float)pr.x, (float)pr.y);
             }
         }
     if (threadIdx.x != 0) return;
@@ -116,12 +121,13 @@ __global__ __launch_bounds__(256) void plan_step_kernel(PlanArgs a) {
         GemmDesc g{};
         g.alpha = 1.f;
         const bool use = fa[s] != nullptr || s == copy_slot;
-        g.active = use ? (a.plain && a.plain[b] ? 2 : 1) : 0;
+        g.active = use ? (plain ? 2 : 1) : 0;
         if (use) {
             g.A = fa[s];
             g.opA = fo[s];
             g.Abf = fb[s];
             g.conjA = fo[s];
+            g.colour = colour;
             g.B = (a.compose && first_op) ? nullptr : a.X[loc] + (long long)b * a.xstride;
             g.C = a.X[loc ^ 1] + (long long)b * a.xstride;
             if (a.dense) {
@@ -129,7 +135,7 @@ __global__ __launch_bounds__(256) void plan_step_kernel(PlanArgs a) {
             } else if (s == first_table || s == copy_slot) {
                 g.kscale = a.pre + (long long)b * d;
             }
-            if ((a.phased || a.strang) && (s == last || s == copy_slot) && (s != 0 || !a.dense))
+            if ((a.phased || a.strang || colour) && (s == last || s == copy_slot) && (s != 0 || !a.dense))
                 g.rscale = a.post + (long long)b * d;
             loc ^= 1;
             first_op = false;
@@ -1356,6 +1362,7 @@ hipError_t plan_step(const PlanLaunch& p, hipStream_t st) {
     a.xstride = p.xstride;
     a.loc = p.loc;
     a.plain = p.plain;
+    a.colour = p.colour;
     a.compose = p.compose;
     a.slots = p.slots;
     a.all_cached = p.all_cached;

@@ -257,11 +257,16 @@ redo_status compose_pairs(redo_table_s* t, int precision, long long I, int N, co
 
 }  // namespace
 
-hipError_t chain_products(int d, int B, int fp32, bool exact_a, const float2* X, bool given, long long xstride,
-                          int* plain, StepProducts* out, hipStream_t st) {
-    const bool split = fp32 < 2 && d >= 192;
-    *out = StepProducts{split ? (exact_a ? GEMM_FP16_EXACT_A : GEMM_FP16) : fp32, fp32, split && given ? plain : nullptr};
-    return out->plain ? state_columns(d, B, X, xstride, plain, st) : hipSuccess;
+hipError_t chain_products(const redo_table_s* t, int B, int precision, const float2* X, bool given, int* plain,
+                          StepProducts* out, hipStream_t st) {
+    const int d = t->desc.d;
+    const bool split = precision < 2 && d >= 192;
+    const bool panels = precision == 2 && t->cache_bf && t->cache_bf_conj && all_cached(t) && cgemm_big(d, B);
+    out->prec = split ? (all_cached(t) ? GEMM_FP16 : GEMM_FP16_EXACT_A) : precision;
+    out->fp32 = precision;
+    out->plain = split && given ? plain : nullptr;
+    out->colour = (split || panels) && t->desc.drift_is_diag ? t->colour : nullptr;
+    return out->plain ? state_columns(d, B, X, t->entry_elems, plain, st) : hipSuccess;
 }
 
 size_t large_workspace_bytes(const redo_table_s* t, int op, int B, int N) {
@@ -325,7 +330,7 @@ redo_status large_chain(redo_table_s* t, int precision, const float* u, const in
     REDO_HIP(fill_int(w.loc, B, 0, st));
     const int S = launch_slots(t);
     StepProducts prod;
-    REDO_HIP(chain_products(d, B, gemm_prec(precision), !all_cached(t), X[0], X0 != nullptr, mat, w.plain, &prod, st));
+    REDO_HIP(chain_products(t, B, gemm_prec(precision), X[0], X0 != nullptr, w.plain, &prod, st));
     for (int n = 0; n < N; ++n) {
         PlanLaunch p = plan_base(t);
         p.codes = w.codes + (size_t)n * t->desc.K;
@@ -337,6 +342,7 @@ redo_status large_chain(redo_table_s* t, int precision, const float* u, const in
         p.X1 = X[1];
         p.loc = w.loc;
         p.plain = prod.plain;
+        p.colour = prod.colour;
         p.pre = w.pre;
         p.post = w.post;
         p.pstar = w.pstar;

@@ -49,6 +49,7 @@ struct PlanLaunch {
     float2* X1;
     long long xstride;
     int* loc;
+    const unsigned* colour;   // gauge of the factors, or null
     const int* plain;        // split FP16: the instances that stay in FP32, or null
     int compose, slots, all_cached;
     const uint16_t* cache_bf;   // pre-split BF16 panels of the cache (split-BF16 products), or null
@@ -69,16 +70,19 @@ hipError_t plan_step(const PlanLaunch& p, hipStream_t st);
 // that leaves the others out.
 struct StepProducts {
     int prec, fp32;
-    const int* plain;   // [B] or null: no such instances
+    const int* plain;        // [B] or null: no such instances
+    const unsigned* colour;   // the gauge in which the factors are real, or null
     hipError_t run(int d, int batch, const GemmDesc* descs, hipStream_t st, int role) const {
-        const hipError_t e = cgemm_batched(d, batch, descs, prec, st, role);
+        const hipError_t e = cgemm_batched(d, batch, descs, prec | (colour ? GEMM_REAL : 0), st, role);
         return e == hipSuccess && plain ? cgemm_batched(d, batch, descs, fp32, st, role, 2) : e;
     }
 };
-// fp32: 0 (4M), 1 (3M) or 2 (split BF16, kept); exact_a: digit operators among the factors; plain:
-// B ints of scratch, filled from the states X if the caller gave them
-hipError_t chain_products(int d, int B, int fp32, bool exact_a, const float2* X, bool given, long long xstride,
-                          int* plain, StepProducts* out, hipStream_t st);
+// Where the generators allow it (collective and single-spin drives) the factors are taken as real:
+// split FP16 products, and split BF16 ones whose factors all come from panels into 128-row tiles.
+// precision: 0 (4M), 1 (3M) or 2 (split BF16); plain: B ints of scratch, filled from the states X if
+// the caller gave them
+hipError_t chain_products(const redo_table_s* t, int B, int precision, const float2* X, bool given, int* plain,
+                          StepProducts* out, hipStream_t st);
 
 // inactive_mode: 0 skip the entry, 1 copy op(B) into C, 2 copy op(A) into C
 hipError_t fill_descs(GemmDesc* descs, int count, const float2* A, long long sA, int opA, const float2* B,

@@ -173,6 +173,9 @@ struct redo_table_s {
     // (bit q of the basis index): n, and the 2 x 2 terms [K][n][2][2] in FP64; else 0
     int kron_n = 0;
     double2* kron_s = nullptr;
+    // the generators are imaginary in a diagonal gauge D = diag(i^c), that is every factor is D Q D^*
+    // with Q real: the colours c as masks of all ones or zero [d] (d >= 128), or null
+    unsigned* colour = nullptr;
 };
 
 constexpr int SPAT_WMAX = 16;
@@ -293,6 +296,8 @@ struct GemmDesc {
     const float2* addend;  // C += addend (d x d) after alpha, or null
     const uint16_t* Abf;   // op(A) as pre-split BF16 panels (split_panels layout), or null;
                            // read by the split-BF16 product in place of A, which stays valid
+    const unsigned* colour;  // GEMM_REAL: op(A) = D Q D^* with Q real, D = diag(i^colour), colours as masks:
+                             // the product is Q op(B) (the caller's scalings hold D and D^*); else null
 };
 static_assert(sizeof(GemmDesc) % 8 == 0, "desc alignment");
 
@@ -308,12 +313,17 @@ constexpr int GEMM_ROLE_STEP = 0, GEMM_ROLE_EXPM = 1, GEMM_ROLE_REPROJECT = 2, G
               GEMM_ROLE_GRAM = 4;
 // only: FP32 products of the entries with this `active` alone (0: of every active one); split FP16
 // runs those with active == 1
-constexpr int GEMM_FP16 = 3, GEMM_FP16_EXACT_A = 4;
+// GEMM_REAL: a flag, every entry with factors real in a gauge (split FP16; split BF16 with panels and
+// 128-row tiles)
+constexpr int GEMM_FP16 = 3, GEMM_FP16_EXACT_A = 4, GEMM_REAL = 16;
+// 128-row tiles: enough of them to fill the card
+inline bool cgemm_big(int d, int batch) { return d % 128 == 0 && (long long)(d / 128) * (d / 64) * batch >= 512; }
 hipError_t cgemm_batched(int d, int batch, const GemmDesc* descs, int precision, hipStream_t st, int role = 0, int only = 0);
 // the split-BF16 launch behind cgemm_batched (cgemm_bf16.hip): 128 x 64 tiles when big, else 64 x 64
 hipError_t cgemm_bf16_launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role, bool big);
-// the split-FP16 launch (cgemm_fp16.hip); exact_a: every bit of A, where the sums are short
-hipError_t cgemm_fp16_launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role, bool big, bool exact_a);
+// the split-FP16 launch (cgemm_split.hip); exact_a: every bit of A, where the sums are short
+hipError_t cgemm_fp16_launch(int d, int batch, const GemmDesc* descs, hipStream_t st, int role, bool big, bool exact_a, bool real);
+hipError_t cgemm_bf16_real_launch(int d, int batch, const GemmDesc* descs, hipStream_t st);
 
 // launch timing (profile.cpp)
 bool profiling_on();

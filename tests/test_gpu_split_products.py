@@ -86,3 +86,52 @@ def test_starts_given_by_the_caller(kind):
         n = np.linalg.norm(ref, axis=0)
         e = np.linalg.norm(U[b].cpu().numpy() - ref, axis=0)
         assert (e <= TOL * n).all()
+
+
+def spins(n, B, N, kinds, seed):
+    """A collective signed drive, x or y on each spin: real and imaginary entries in one generator,
+    real factors in a diagonal gauge."""
+    d = 2 ** n
+    S = np.zeros((d, d), complex)
+    for q, k in enumerate(kinds):
+        i = np.arange(d)
+        j = i ^ (1 << q)
+        S[i, j] += 0.5 if k == "x" else np.where(i >> q & 1, 0.5j, -0.5j)
+    gen = np.random.default_rng(seed)
+    u = (gen.uniform(-1, 1, (B, N, 1)) * 3e5).astype(np.float32)
+    u[:, 1] = 0.0   # a step without a factor
+    return W.Problem("spins", d, 1, False, gen.uniform(-2e4, 2e4, (1, d)), True, S[None], None, 1e-6,
+                     3e5 / (16 ** 2 - 1), 16, 2, u, u_scale=3e5)
+
+
+@pytest.mark.parametrize("n,B,cached", [(8, 1, True), (8, 2, False), (8, 65, True), (8, 64, False), (9, 17, True),
+                                        (9, 16, False), (10, 5, True)])
+@pytest.mark.parametrize("kinds", ["x", "y", "xy"])
+def test_real_factors_vs_fp64(n, B, cached, kinds):
+    p = spins(n, B, 4, (kinds * n)[:n], 10 * n + B)
+    t = R().RedoTable.from_problem(p)
+    if cached:
+        t.cache_levels()
+    u = torch.tensor(p.u).cuda()
+    U, _, _ = t.chain(u, precision=R().PREC_F32, reproject_every=3)
+    V, _, _ = t.chain(u, X0=torch.eye(p.d, dtype=torch.complex64, device="cuda").repeat(B, 1, 1) * 3.0)   # FP32 products
+    for b in {0, B // 2, B - 1}:
+        ref = O.chain(steps_of(p, b))
+        assert relerr(U[b], ref) < TOL and relerr(V[b], 3.0 * ref) < TOL
+
+
+@pytest.mark.parametrize("n,B", [(7, 300), (8, 64), (8, 3), (9, 17)])
+@pytest.mark.parametrize("kinds", ["x", "xy"])
+def test_real_factors_bf16_panels_vs_fp64(n, B, kinds):
+    """Split BF16 with and without panels (real factors need panels, 128-row tiles and symmetric
+    levels): 2^-16 per product, of which there are 4."""
+    p = spins(n, B, 4, (kinds * n)[:n], 20 * n + B)
+    t = R().RedoTable.from_problem(p)
+    t.cache_levels()
+    u = torch.tensor(p.u).cuda()
+    U, _, _ = t.chain(u, precision=R().PREC_BF16X3)
+    t.cache_split_bf16()
+    V, _, _ = t.chain(u, precision=R().PREC_BF16X3)
+    for b in {0, B // 2, B - 1}:
+        ref = O.chain(steps_of(p, b))
+        assert relerr(U[b], ref) < 4 * 2.0 ** -16 and relerr(V[b], ref) < 4 * 2.0 ** -16
