@@ -31,15 +31,20 @@ struct MvDesc {
     int conj_scales;      // 1: conj(pre), conj(post)
 };
 
-// y = post . op(F) (pre . x), one workgroup of 16 waves per 16 rows of y reading those
-// rows of op(F) whole (16 d complex entries, 128 KiB at d = 1024) in blocks of 16
+// y = post . op(F) (pre . x), one workgroup of 8 waves per 8 rows of y reading those
+// rows of op(F) whole (8 d complex entries, 64 KiB at d = 1024) in blocks of 16
 // independent loads per thread, the scaled input in LDS (FP64, 16 d bytes), FP64
 // products and sums of the FP32 factor entries: nothing leaves the workgroup
 // before the result, so one factor application is one launch and the summation order
-// is fixed.  blockIdx.y runs over the instances of up to two independent chains, the
-// forward chain and the backward scan: y < B takes descs0[y], y >= B descs1[y - B].
-constexpr int MV_R = 16;
-constexpr int MV_NT = 1024;
+// is fixed.  A launch is bound by its chain of latencies (descriptor, factor and input, sum,
+// store), so the first block of the factor is on its way before the input is staged, and the two
+// directions of one chain at d = 1024 are 256 workgroups, one per CU: 7.8 us per step against 8.8
+// for 16 rows with the factor loaded after the input (16 MiB: 3.3 us at this card's copy rate; the
+// rest is the launch itself: touching the next factor's lines ahead changed nothing).
+// blockIdx.y runs over the instances of up to two independent chains, the forward chain and
+// the backward scan: y < B takes descs0[y], y >= B descs1[y - B].
+constexpr int MV_R = 8;
+constexpr int MV_NT = 512;
 static_assert(MV_NT / 64 == MV_R && 64 % MV_R == 0, "one wave per row, column groups of the adjoint");
 constexpr int MV_U = 16;    // loads per thread in flight
 
@@ -51,6 +56,13 @@ typedef __attribute__((address_space(1))) const mv_v2 mv_gv2;
 __device__ inline float2 mv_load(const float2* p, long long i) {
     const mv_v2 v = ((mv_gv2*)p)[i];
     return make_float2(v.x, v.y);
+}
+
+typedef double mv_d2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) const mv_d2 mv_gd2;
+__device__ inline double2 mv_load2(const double2* p, int i) {
+    const mv_d2 v = ((mv_gd2*)p)[i];
+    return make_double2(v.x, v.y);
 }
 
 __device__ inline double2 mv_scale(const MvDesc& m, const double2* s, int i) {
@@ -73,14 +85,19 @@ __device__ inline void zfma_fc(double2& a, float2 f, double2 x) {
     a.y += (double)f.x * x.y - (double)f.y * x.x;
 }
 
+// U > 0: d is a multiple of 64 U and every load of a block is in range; U = 0: any d, blocks of MV_U
+template <int U>
 __global__ __launch_bounds__(MV_NT) void matvec_kernel(int d, const MvDesc* __restrict__ descs0,
                                                        const MvDesc* __restrict__ descs1, int B) {
     extern __shared__ double2 xs[];   // [d]: pre . x
     __shared__ double2 red[MV_NT / 64][MV_R];
+    constexpr int NU = U ? U : MV_U;
     const int z = blockIdx.y;
     const MvDesc m = z < B ? descs0[z] : descs1[z - B];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int r0 = blockIdx.x * MV_R;
+    // neighbouring row blocks on one XCD: they share the lines of an adjoint factor
+    const int nb = gridDim.x, rb = nb % 8 == 0 ? (int)(blockIdx.x % 8 * (nb / 8) + blockIdx.x / 8) : (int)blockIdx.x;
+    const int r0 = rb * MV_R;
     if (!m.F) {   // identity factor: copy with the scalings
         const int r = r0 + t;
         if (t < MV_R && r < d) {
@@ -90,27 +107,53 @@ __global__ __launch_bounds__(MV_NT) void matvec_kernel(int d, const MvDesc* __re
         }
         return;
     }
-    for (int c = t; c < d; c += MV_NT) xs[c] = mv_input(m, c);
+    // y_r = sum_c op(F)_rc x_c.  Adjoint: lanes over the MV_R rows (one segment of row c of F) and
+    // 64 / MV_R column groups, waves over the others (64 in all), column c = 64 j + group.  As given:
+    // wave w takes row r0 + w, lanes over columns c = lane + 64 j (512 contiguous bytes per load)
+    const int r = r0 + (m.adj ? lane % MV_R : wv);
+    const int c0 = m.adj ? lane / MV_R + (64 / MV_R) * wv : lane;
+    const long long step = m.adj ? 64LL * d : 64;   // between the loads of a block
+    const float2* src = m.F + (m.adj ? (long long)c0 * d + r : (long long)r * d + c0);
+    const bool ok = U || r < d;
+    float2 f[NU];
+    auto load = [&](int cb) {
+#pragma unroll
+        for (int j = 0; j < NU; ++j)
+            f[j] = U || (ok && cb + c0 + 64 * j < d) ? mv_load(src, (cb / 64 + j) * step) : make_float2(0.f, 0.f);
+    };
+    // the input is asked for before the factor, and waited for alone
+    constexpr int NX = U == 16 ? 2 : 1;   // all of it at d = 1024
+    double2 xv[NX], pv[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int c = U >= 8 ? t + i * MV_NT : min(t, d - 1);
+        xv[i] = mv_load2(m.x, c);
+        pv[i] = mv_load2(m.pre ? m.pre : m.x, c);
+    }
+    load(0);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int c = t + i * MV_NT;
+        // a factor of 1 where there is no scaling: a branch would take the load of pv with it
+        const double2 p = m.pre ? make_double2(pv[i].x, m.conj_scales ? -pv[i].y : pv[i].y) : make_double2(1.0, 0.0);
+        if (U >= 8 || c < d) xs[c] = zmul(p, xv[i]);
+    }
+    for (int c = t + NX * MV_NT; c < d; c += MV_NT) xs[c] = mv_input(m, c);
     __syncthreads();
     double2 acc = make_double2(0.0, 0.0);
-    if (m.adj) {
-        // y_r = sum_c conj(F[c][r]) x_c: lanes over the MV_R rows (one segment of row c of F)
-        // and 64 / MV_R column groups, waves over the others (64 in all); column c = 64 j + group
-        const int rl = lane % MV_R, cg = lane / MV_R + (64 / MV_R) * wv, r = r0 + rl;
-        const bool ok = r < d;
-        for (int cb = 0; cb < d; cb += 64 * MV_U) {
-            float2 f[MV_U];
+    for (int cb = 0; cb < d; cb += 64 * NU) {
+        if (cb > 0) load(cb);
+        if (m.adj) {
 #pragma unroll
-            for (int j = 0; j < MV_U; ++j) {
-                const int c = cb + cg + 64 * j;
-                f[j] = (ok && c < d) ? mv_load(m.F, (long long)c * d + r) : make_float2(0.f, 0.f);
-            }
+            for (int j = 0; j < NU; ++j)
+                if (U || cb + c0 + 64 * j < d) zfma_fc(acc, f[j], xs[cb + c0 + 64 * j]);
+        } else {
 #pragma unroll
-            for (int j = 0; j < MV_U; ++j) {
-                const int c = cb + cg + 64 * j;
-                if (c < d) zfma_fc(acc, f[j], xs[c]);
-            }
+            for (int j = 0; j < NU; ++j)
+                if (U || cb + c0 + 64 * j < d) zfma_f(acc, f[j], xs[cb + c0 + 64 * j]);
         }
+    }
+    if (m.adj) {
 #pragma unroll
         for (int o = MV_R; o < 64; o <<= 1) {
             acc.x += __shfl_xor(acc.x, o);
@@ -118,23 +161,6 @@ __global__ __launch_bounds__(MV_NT) void matvec_kernel(int d, const MvDesc* __re
         }
         if (lane < MV_R) red[wv][lane] = acc;
     } else {
-        // y_r = sum_c F[r][c] x_c: wave w takes row r0 + w, lanes over columns c = lane + 64 j
-        // (512 contiguous bytes of the row per load), then a wave sum
-        const int r = r0 + wv;
-        const bool ok = r < d;
-        for (int cb = 0; cb < d; cb += 64 * MV_U) {
-            float2 f[MV_U];
-#pragma unroll
-            for (int j = 0; j < MV_U; ++j) {
-                const int c = cb + lane + 64 * j;
-                f[j] = (ok && c < d) ? mv_load(m.F, (long long)r * d + c) : make_float2(0.f, 0.f);
-            }
-#pragma unroll
-            for (int j = 0; j < MV_U; ++j) {
-                const int c = cb + lane + 64 * j;
-                if (c < d) zfma_f(acc, f[j], xs[c]);
-            }
-        }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
             acc.x += __shfl_xor(acc.x, o);
@@ -143,16 +169,26 @@ __global__ __launch_bounds__(MV_NT) void matvec_kernel(int d, const MvDesc* __re
         if (lane == 0) red[0][wv] = acc;
     }
     __syncthreads();
-    const int r = r0 + t;
-    if (t < MV_R && r < d) {
+    const int ro = r0 + t;
+    if (t < MV_R && ro < d) {
         double2 v = red[0][t];
         if (m.adj) {
 #pragma unroll
             for (int w = 1; w < MV_NT / 64; ++w) v = make_double2(v.x + red[w][t].x, v.y + red[w][t].y);
         }
-        if (m.post) v = zmul(mv_scale(m, m.post, r), v);
-        m.y[r] = v;
+        if (m.post) v = zmul(mv_scale(m, m.post, ro), v);
+        m.y[ro] = v;
     }
+}
+
+using MatvecKernel = void (*)(int, const MvDesc*, const MvDesc*, int);
+MatvecKernel matvec_for(int d) {
+    return d % 1024 == 0  ? matvec_kernel<16>
+           : d % 512 == 0 ? matvec_kernel<8>
+           : d % 256 == 0 ? matvec_kernel<4>
+           : d % 128 == 0 ? matvec_kernel<2>
+           : d % 64 == 0  ? matvec_kernel<1>
+                          : matvec_kernel<0>;
 }
 
 struct StatePlan {
@@ -542,9 +578,10 @@ redo_status state_grape(redo_table_s* t, const float* u, const int* n_steps, int
     p.Chi = w.Chi;
     p.all = PS > 1 ? 1 : 0;
     const int nrt = (d + MV_R - 1) / MV_R;
+    const MatvecKernel matvec = matvec_for(d);
     if (S == 0) return fail(REDO_ERR_UNSUPPORTED, "no factor slots");
     const size_t mv_lds = sizeof(double2) * (size_t)d;
-    REDO_HIP(hipFuncSetAttribute((const void*)matvec_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mv_lds));
+    REDO_HIP(hipFuncSetAttribute((const void*)matvec, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mv_lds));
     if (p.all) {
         // every step planned at once: step n of the forward chain and step N - 1 - n of the
         // backward scan (independent chains) share each launch
@@ -554,7 +591,7 @@ redo_status state_grape(redo_table_s* t, const float* u, const int* n_steps, int
             const MvDesc* fw = w.descs + (size_t)n * S * B;
             const MvDesc* bw = w.descs + (size_t)(N + N - 1 - n) * S * B;
             for (int i = 0; i < S; ++i)
-                hipLaunchKernelGGL(matvec_kernel, dim3(nrt, 2 * B), dim3(MV_NT), mv_lds, st, d, fw + (size_t)i * B,
+                hipLaunchKernelGGL(matvec, dim3(nrt, 2 * B), dim3(MV_NT), mv_lds, st, d, fw + (size_t)i * B,
                                    bw + (size_t)i * B, B);
             REDO_HIP(hipGetLastError());
         }
@@ -564,7 +601,7 @@ redo_status state_grape(redo_table_s* t, const float* u, const int* n_steps, int
             p.backward = backward;
             hipLaunchKernelGGL(state_plan_kernel, dim3(B), dim3(256), 0, st, p);
             for (int i = 0; i < S; ++i)
-                hipLaunchKernelGGL(matvec_kernel, dim3(nrt, B), dim3(MV_NT), mv_lds, st, d, w.descs + (size_t)i * B,
+                hipLaunchKernelGGL(matvec, dim3(nrt, B), dim3(MV_NT), mv_lds, st, d, w.descs + (size_t)i * B,
                                    (const MvDesc*)nullptr, B);
             return hipGetLastError();
         };

@@ -122,3 +122,14 @@ def test_state_grape_per_step_plans_equal_one_plan_d128():
         assert torch.equal(F[b:b + 1], F1) and torch.equal(ov[b:b + 1], ov1) and torch.equal(grad[b:b + 1], g1)
     _check(p.subset([5, 63]), psi0[[5, 63]], psif[[5, 63]], F.cpu().numpy()[[5, 63]], ov.cpu().numpy()[[5, 63]],
            grad.cpu().numpy()[[5, 63]])
+
+
+@pytest.mark.parametrize("n,B,N", [(5, 2, 6), (6, 1, 5), (8, 3, 5), (9, 2, 4), (10, 1, 3)])
+def test_state_grape_block_widths_vs_oracle(n, B, N):
+    """Every width of a factor block (d = 64 .. 1024, and below 64), ragged, a step without a factor."""
+    p = W.nmr_chain(n, B, N, 2e-6, 4, 2, 600 + n, species=None, targets=False)
+    p.u[:, 1] = 0.0
+    p.n_steps = np.array([N, max(1, N - 1), N][:B], np.int32)
+    psi0, psif = _states(p.d, B, n)
+    for cache in (False, True):
+        _check(p, psi0, psif, *_run(p, psi0, psif, cache=cache))
