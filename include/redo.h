@@ -62,7 +62,10 @@ typedef enum {
 } redo_status;
 
 typedef enum {
-    REDO_PREC_F32 = 0,     /* FP32 complex products, four real products per complex one */
+    /* FP32 complex products, four real products per complex one.  In the chains at d >= 192 both FP32
+     * forms run as split FP16 with FP32 accumulation (errors below either form's) for every instance
+     * whose start is the identity or has columns of norm in [1/2, 2] (or zero) */
+    REDO_PREC_F32 = 0,
     REDO_PREC_F32_3M = 1,  /* FP32, three real products (Gauss) per complex one; d >= 128 */
     REDO_PREC_BF16X3 = 2   /* split BF16: hi*hi + hi*lo + lo*hi, FP32 accumulate; d >= 128 */
 } redo_precision;

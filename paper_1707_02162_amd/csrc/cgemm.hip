@@ -23,18 +23,38 @@
 namespace redo {
 namespace {
 
+// global -> registers for one stage; AH, BH: op(A) = A^H, op(B) = B^H
+template <int BM, int BN, bool AH, bool BH>
+__device__ inline void load_tiles(const GemmDesc& g, int d, int i0, int j0, int k0, float4 (&ra)[GCfg<BM, BN>::AV],
+                                  float4 (&rb)[GCfg<BM, BN>::BV]) {
+    using C = GCfg<BM, BN>;
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int m = 0; m < C::AV; ++m) {
+        const int e = t + C::THREADS * m;
+        ra[m] = AH ? ldg4(g.A + (long long)(k0 + e / (BM / 2)) * d + i0 + 2 * (e % (BM / 2)))
+                   : ldg4(g.A + (long long)(i0 + e / (KT / 2)) * d + k0 + 2 * (e % (KT / 2)));
+    }
+#pragma unroll
+    for (int m = 0; m < C::BV; ++m) {
+        const int e = t + C::THREADS * m;
+        rb[m] = BH ? ldg4(g.B + (long long)(j0 + e / (KT / 2)) * d + k0 + 2 * (e % (KT / 2)))
+                   : ldg4(g.B + (long long)(k0 + e / (BN / 2)) * d + j0 + 2 * (e % (BN / 2)));
+    }
+}
+
 // registers -> LDS (k-major tiles As[k][i], Bs[k][j]); conjugation, transposition and the k-scaling
-// here, the stage's KT scaling factors read from LDS (KSL: ks, prefetched) or from global memory
-template <int BM, int BN, bool KSL>
-__device__ inline void store_stage(const GemmDesc& g, int k0, const float4 (&ra)[GCfg<BM, BN>::AV],
-                                   const float4 (&rb)[GCfg<BM, BN>::BV], const float2* ks, float2* As, float2* Bs) {
+// (the stage's KT factors in ks, or null) here
+template <int BM, int BN, bool AH, bool BH>
+__device__ inline void store_stage(const float4 (&ra)[GCfg<BM, BN>::AV], const float4 (&rb)[GCfg<BM, BN>::BV],
+                                   const float2* ks, float2* As, float2* Bs) {
     using C = GCfg<BM, BN>;
     const int t = threadIdx.x;
 #pragma unroll
     for (int m = 0; m < C::AV; ++m) {
         const int e = t + C::THREADS * m;
         const float4 v = ra[m];
-        if (g.opA == 0) {
+        if constexpr (!AH) {
             const int row = e / (KT / 2), kq = e % (KT / 2);
             As[(2 * kq) * C::LDA + row] = f2(v.x, v.y);
             As[(2 * kq + 1) * C::LDA + row] = f2(v.z, v.w);
@@ -47,11 +67,11 @@ __device__ inline void store_stage(const GemmDesc& g, int k0, const float4 (&ra)
     for (int m = 0; m < C::BV; ++m) {
         const int e = t + C::THREADS * m;
         const float4 v = rb[m];
-        if (g.opB == 0) {
+        if constexpr (!BH) {
             const int kr = e / (BN / 2), jq = e % (BN / 2);
             float2 a = f2(v.x, v.y), b = f2(v.z, v.w);
-            if (g.kscale) {
-                const float2 s = KSL ? ks[kr] : ldg2(g.kscale + k0 + kr);
+            if (ks) {
+                const float2 s = ks[kr];
                 a = cmul(s, a);
                 b = cmul(s, b);
             }
@@ -59,9 +79,9 @@ __device__ inline void store_stage(const GemmDesc& g, int k0, const float4 (&ra)
         } else {
             const int row = e / (KT / 2), kq = e % (KT / 2);
             float2 a = f2(v.x, -v.y), b = f2(v.z, -v.w);
-            if (g.kscale) {
-                a = cmul(KSL ? ks[2 * kq] : ldg2(g.kscale + k0 + 2 * kq), a);
-                b = cmul(KSL ? ks[2 * kq + 1] : ldg2(g.kscale + k0 + 2 * kq + 1), b);
+            if (ks) {
+                a = cmul(ks[2 * kq], a);
+                b = cmul(ks[2 * kq + 1], b);
             }
             Bs[(2 * kq) * C::LDB + row] = a;
             Bs[(2 * kq + 1) * C::LDB + row] = b;
@@ -69,51 +89,17 @@ __device__ inline void store_stage(const GemmDesc& g, int k0, const float4 (&ra)
     }
 }
 
-// MODE 0: 4M, MODE 1: 3M (Gauss).  ROLE separates the instantiations that the
-// method's chain step products (0), the plain-exponential comparison point (1), the
-// Newton-Schulz re-projections (2) and the composition of single step propagators (3)
-// launch, so that profiles attribute their time apart; the code is the same.  The Gram
-// role (4, a re-projection's A^H A) runs only the tiles that meet the upper triangle and
-// mirrors them (gram_tile, store_c).
-template <int BM, int BN, int MODE, int ROLE>
-// at least three waves per SIMD: the 3M form then keeps its 96 accumulators in VGPRs
-// (167 registers, no spills) instead of two waves with AGPRs, 240 -> 218 ms for 4096
-// products at d = 1024; the LDS already bounds every form at three workgroups per CU
-__global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int only, const GemmDesc* __restrict__ descs) {
+// One output tile.  A stage's tiles are loaded two stages ahead of their products and go to LDS
+// one ahead, between the matrix instructions: op(A), op(B) and the presence of a k-scaling are
+// template parameters, since the compiler moves nothing across a branch.  The order of the sums
+// over k is that of the index.
+template <int BM, int BN, int MODE, bool GRAM, bool AH, bool BH, bool SCALED>
+__device__ __forceinline__ void fp32_tile(const GemmDesc& g, int d, int i0, int j0, float2 (*As)[KT * GCfg<BM, BN>::LDA],
+                                          float2 (*Bs)[KT * GCfg<BM, BN>::LDB], float2 (*Ks)[KT]) {
     using C = GCfg<BM, BN>;
-    __shared__ float2 As[2][KT * C::LDA];
-    __shared__ float2 Bs[2][KT * C::LDB];
-    __shared__ float2 Ks[3][KT];   // k-scaling of stages kt, kt + 1, kt + 2
-    constexpr bool GRAM = ROLE == GEMM_ROLE_GRAM;
-    const int tiles_n = d / BN;
-    const int ntile = GRAM ? (int)gram_tile_count<BM, BN>(d) : (d / BM) * tiles_n;
-    int bid = blockIdx.x;
-    const int nb = gridDim.x;
-    if (nb % NXCD == 0) bid = (bid % NXCD) * (nb / NXCD) + bid / NXCD;
-    const int be = bid / ntile, tile = bid % ntile;
-    const GemmDesc g = descs[be];
-    if (only ? g.active != only : !g.active) return;
-    int i0, j0;
-    if constexpr (GRAM) {
-        gram_tile<BM, BN>(d, tile, i0, j0);
-    } else {
-        i0 = (tile / tiles_n) * BM;
-        j0 = (tile % tiles_n) * BN;
-    }
-    if (g.A == nullptr || g.B == nullptr) {
-        copy_tile(g, d, i0, j0, BM, BN);
-        return;
-    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wi0 = (wave >> 1) * C::WM, wj0 = (wave & 1) * C::WN;
     const int nk = d / KT;
-    // k-scaling through LDS for the large tile (big batches: 1.1 % faster at d = 1024); the 64 x 64
-    // tile of small batches, latency-bound at two waves per SIMD, was 2 % slower with it
-    constexpr bool KSL = BM == 128;
-    if constexpr (KSL) {
-        ks_fetch(g, 0, Ks);
-        if (nk > 1) ks_fetch(g, 1, Ks);
-    }
     constexpr int NACC = MODE == 0 ? 2 : 3;
     floatx16 acc[NACC][C::FM][C::FN];
 #pragma unroll
@@ -126,18 +112,18 @@ __global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int only, const Ge
                 for (int r = 0; r < 16; ++r) acc[a][ib][jb][r] = 0.f;
 
     float4 ra[C::AV], rb[C::BV];
-    load_stage<BM, BN>(g, d, i0, j0, 0, ra, rb);
-    if (KSL && g.kscale != nullptr) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // Ks[0], Ks[1] landed
-        __syncthreads();
-    }
-    store_stage<BM, BN, KSL>(g, 0, ra, rb, Ks[0], As[0], Bs[0]);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_stage<BM, BN>(g, d, i0, j0, (kt + 1) * KT, ra, rb);
-        // slot (kt + 2) % 3 was last read by the store of stage kt - 1, before the previous barrier
-        if (KSL && kt + 2 < nk) ks_fetch(g, kt + 2, Ks);
+    float2 kreg = f2(0.f, 0.f);   // k-scaling on its way to LDS (every thread one of the stage's KT factors)
+    auto load = [&](int kt) { load_tiles<BM, BN, AH, BH>(g, d, i0, j0, kt * KT, ra, rb); };
+    auto store = [&](int kt, int buf) {
+        store_stage<BM, BN, AH, BH>(ra, rb, SCALED ? Ks[kt % 3] : nullptr, As[buf], Bs[buf]);
+    };
+    auto load_k = [&](int kt) {
+        if constexpr (SCALED) kreg = ldg2(g.kscale + kt * KT + (threadIdx.x & (KT - 1)));
+    };
+    auto store_k = [&](int kt) {
+        if constexpr (SCALED) Ks[kt % 3][threadIdx.x & (KT - 1)] = kreg;
+    };
+    auto products = [&](int buf) __attribute__((always_inline)) {
         const float2* Ab = As[buf];
         const float2* Bb = Bs[buf];
 #pragma unroll
@@ -148,50 +134,51 @@ __global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int only, const Ge
             for (int ib = 0; ib < C::FM; ++ib) a[ib] = Ab[kr * C::LDA + wi0 + ib * 32 + (lane & 31)];
 #pragma unroll
             for (int jb = 0; jb < C::FN; ++jb) b[jb] = Bb[kr * C::LDB + wj0 + jb * 32 + (lane & 31)];
+            auto mf = [&](int x, auto pa, auto pb) __attribute__((always_inline)) {
+#pragma unroll
+                for (int ib = 0; ib < C::FM; ++ib)
+#pragma unroll
+                    for (int jb = 0; jb < C::FN; ++jb)
+                        acc[x][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa(a[ib]), pb(b[jb]), acc[x][ib][jb], 0, 0, 0);
+            };
+            auto re = [](float2 v) { return v.x; };
+            auto im = [](float2 v) { return v.y; };
             if constexpr (MODE == 0) {
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[0][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].x, b[jb].x, acc[0][ib][jb], 0, 0, 0);
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[1][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].x, b[jb].y, acc[1][ib][jb], 0, 0, 0);
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[0][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(-a[ib].y, b[jb].y, acc[0][ib][jb], 0, 0, 0);
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[1][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].y, b[jb].x, acc[1][ib][jb], 0, 0, 0);
+                mf(0, re, re);
+                mf(1, re, im);
+                mf(0, [](float2 v) { return -v.y; }, im);
+                mf(1, im, re);
             } else {
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[0][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].x, b[jb].x, acc[0][ib][jb], 0, 0, 0);
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[1][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].y, b[jb].y, acc[1][ib][jb], 0, 0, 0);
-#pragma unroll
-                for (int ib = 0; ib < C::FM; ++ib)
-#pragma unroll
-                    for (int jb = 0; jb < C::FN; ++jb)
-                        acc[2][ib][jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].x + a[ib].y, b[jb].x + b[jb].y,
-                                                                              acc[2][ib][jb], 0, 0, 0);
+                auto sum = [](float2 v) { return v.x + v.y; };
+                mf(0, re, re);
+                mf(1, im, im);
+                mf(2, sum, sum);
             }
         }
-        if (kt + 1 < nk) store_stage<BM, BN, KSL>(g, (kt + 1) * KT, ra, rb, Ks[(kt + 1) % 3], As[buf ^ 1], Bs[buf ^ 1]);
-        if (KSL && g.kscale != nullptr) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this stage's ks_fetch landed
+    };
+    // d >= 64 in multiples of 64: at least four stages
+    load(0);
+    load_k(0);
+    store_k(0);
+    load_k(1);
+    store_k(1);
+    load_k(2);
+    if constexpr (SCALED) __syncthreads();
+    store(0, 0);
+    load(1);
+    __syncthreads();
+    for (int kt = 0; kt + 2 < nk; ++kt) {
+        store_k(kt + 2);
+        store(kt + 1, (kt & 1) ^ 1);
+        load(kt + 2);
+        load_k(min(kt + 3, nk - 1));
+        products(kt & 1);
         __syncthreads();
     }
+    store(nk - 1, (nk - 1) & 1);
+    products((nk - 2) & 1);
+    __syncthreads();
+    products((nk - 1) & 1);
     // epilogue: element (i, j) of a 32x32 block lives in lane j + 32 * ((i / 4) % 2), register 4 * (i / 8) + i % 4
 #pragma unroll
     for (int ib = 0; ib < C::FM; ++ib)
@@ -216,6 +203,62 @@ __global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int only, const Ge
                 if (i == j) v.x += g.beta_identity;
                 store_c<GRAM>(g, d, i, j, v);
             }
+}
+
+// MODE 0: 4M, MODE 1: 3M (Gauss).  ROLE separates the instantiations that the
+// method's chain step products (0), the plain-exponential comparison point (1), the
+// Newton-Schulz re-projections (2) and the composition of single step propagators (3)
+// launch, so that profiles attribute their time apart; the code is the same.  The Gram
+// role (4, a re-projection's A^H A) runs only the tiles that meet the upper triangle and
+// mirrors them (gram_tile, store_c).
+template <int BM, int BN, int MODE, int ROLE>
+// at least three waves per SIMD: the 3M form then keeps its 96 accumulators in VGPRs
+// (167 registers, no spills) instead of two waves with AGPRs, 240 -> 218 ms for 4096
+// products at d = 1024; the LDS already bounds every form at three workgroups per CU
+__global__ __launch_bounds__(256, 3) void cgemm_kernel(int d, int only, const GemmDesc* __restrict__ descs) {
+    using C = GCfg<BM, BN>;
+    __shared__ float2 As[2][KT * C::LDA];
+    __shared__ float2 Bs[2][KT * C::LDB];
+    __shared__ float2 Ks[3][KT];   // k-scaling of stages kt, kt + 1, kt + 2 in turn
+    constexpr bool GRAM = ROLE == GEMM_ROLE_GRAM;
+    const int tiles_n = d / BN;
+    const int ntile = GRAM ? (int)gram_tile_count<BM, BN>(d) : (d / BM) * tiles_n;
+    int bid = blockIdx.x;
+    const int nb = gridDim.x;
+    if (nb % NXCD == 0) bid = (bid % NXCD) * (nb / NXCD) + bid / NXCD;
+    const int be = bid / ntile, tile = bid % ntile;
+    const GemmDesc g = descs[be];
+    if (only ? g.active != only : !g.active) return;
+    int i0, j0;
+    if constexpr (GRAM) {
+        gram_tile<BM, BN>(d, tile, i0, j0);
+    } else {
+        i0 = (tile / tiles_n) * BM;
+        j0 = (tile % tiles_n) * BN;
+    }
+    if (g.A == nullptr || g.B == nullptr) {
+        copy_tile(g, d, i0, j0, BM, BN);
+        return;
+    }
+    if constexpr (GRAM) {
+        fp32_tile<BM, BN, MODE, true, true, false, false>(g, d, i0, j0, As, Bs, Ks);
+    } else if (g.kscale) {
+        if (g.opB) {
+            if (g.opA) fp32_tile<BM, BN, MODE, false, true, true, true>(g, d, i0, j0, As, Bs, Ks);
+            else fp32_tile<BM, BN, MODE, false, false, true, true>(g, d, i0, j0, As, Bs, Ks);
+        } else {
+            if (g.opA) fp32_tile<BM, BN, MODE, false, true, false, true>(g, d, i0, j0, As, Bs, Ks);
+            else fp32_tile<BM, BN, MODE, false, false, false, true>(g, d, i0, j0, As, Bs, Ks);
+        }
+    } else {
+        if (g.opB) {
+            if (g.opA) fp32_tile<BM, BN, MODE, false, true, true, false>(g, d, i0, j0, As, Bs, Ks);
+            else fp32_tile<BM, BN, MODE, false, false, true, false>(g, d, i0, j0, As, Bs, Ks);
+        } else {
+            if (g.opA) fp32_tile<BM, BN, MODE, false, true, false, false>(g, d, i0, j0, As, Bs, Ks);
+            else fp32_tile<BM, BN, MODE, false, false, false, false>(g, d, i0, j0, As, Bs, Ks);
+        }
+    }
 }
 
 template <int BM, int BN, int MODE>
