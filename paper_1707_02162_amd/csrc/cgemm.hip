@@ -17,6 +17,7 @@
 // are mapped to one XCD so its operands are shared in that XCD's L2.
 #include <cstdlib>
 #include <string>
+#include <type_traits>
 
 #include "cgemm_common.h"
 
@@ -90,9 +91,12 @@ __device__ inline void store_stage(const float4 (&ra)[GCfg<BM, BN>::AV], const f
 }
 
 // One output tile.  A stage's tiles are loaded two stages ahead of their products and go to LDS
-// one ahead, between the matrix instructions: op(A), op(B) and the presence of a k-scaling are
+// one ahead, in the middle of a stage's products: op(A), op(B) and the presence of a k-scaling are
 // template parameters, since the compiler moves nothing across a branch.  The order of the sums
-// over k is that of the index.
+// over k is that of the index.  Two products at d = 1024 (64 x 64 tiles, two workgroups per CU, 3M):
+// 134 us with loads one stage ahead and stores after the products, 121 with stores before them,
+// 115 so (84 us at the rate of a large FP32 product); four at d = 512 (one workgroup per CU, 4M)
+// 52.2, 52.2 and 51.8 us.
 template <int BM, int BN, int MODE, bool GRAM, bool AH, bool BH, bool SCALED>
 __device__ __forceinline__ void fp32_tile(const GemmDesc& g, int d, int i0, int j0, float2 (*As)[KT * GCfg<BM, BN>::LDA],
                                           float2 (*Bs)[KT * GCfg<BM, BN>::LDB], float2 (*Ks)[KT]) {
@@ -123,11 +127,11 @@ __device__ __forceinline__ void fp32_tile(const GemmDesc& g, int d, int i0, int 
     auto store_k = [&](int kt) {
         if constexpr (SCALED) Ks[kt % 3][threadIdx.x & (KT - 1)] = kreg;
     };
-    auto products = [&](int buf) __attribute__((always_inline)) {
+    auto products = [&](int buf, auto k0, auto k1) __attribute__((always_inline)) {
         const float2* Ab = As[buf];
         const float2* Bb = Bs[buf];
 #pragma unroll
-        for (int kk = 0; kk < KT; kk += 2) {
+        for (int kk = k0.value; kk < k1.value; kk += 2) {
             const int kr = kk + (lane >> 5);
             float2 a[C::FM], b[C::FN];
 #pragma unroll
@@ -156,6 +160,9 @@ __device__ __forceinline__ void fp32_tile(const GemmDesc& g, int d, int i0, int 
             }
         }
     };
+    using K0 = std::integral_constant<int, 0>;
+    using KH = std::integral_constant<int, KT / 2>;
+    using K1 = std::integral_constant<int, KT>;
     // d >= 64 in multiples of 64: at least four stages
     load(0);
     load_k(0);
@@ -168,17 +175,18 @@ __device__ __forceinline__ void fp32_tile(const GemmDesc& g, int d, int i0, int 
     load(1);
     __syncthreads();
     for (int kt = 0; kt + 2 < nk; ++kt) {
+        products(kt & 1, K0{}, KH{});
         store_k(kt + 2);
         store(kt + 1, (kt & 1) ^ 1);
         load(kt + 2);
         load_k(min(kt + 3, nk - 1));
-        products(kt & 1);
+        products(kt & 1, KH{}, K1{});
         __syncthreads();
     }
     store(nk - 1, (nk - 1) & 1);
-    products((nk - 2) & 1);
+    products((nk - 2) & 1, K0{}, K1{});
     __syncthreads();
-    products((nk - 1) & 1);
+    products((nk - 1) & 1, K0{}, K1{});
     // epilogue: element (i, j) of a 32x32 block lives in lane j + 32 * ((i / 4) % 2), register 4 * (i / 8) + i % 4
 #pragma unroll
     for (int ib = 0; ib < C::FM; ++ib)

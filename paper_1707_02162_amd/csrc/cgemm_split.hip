@@ -2,6 +2,8 @@
 // the FP32 step products of the large-d chains in split FP16, for operands whose columns have
 // norms near one, that is for unitary factors and states; and, for factors that are real in a
 // diagonal gauge, also the split-BF16 ones from panels.
+#include <type_traits>
+
 #include "cgemm_common.h"
 
 namespace redo {
@@ -25,7 +27,7 @@ namespace {
 // Factors real in a gauge (collective and single-spin drives, REAL): 12 d^3, 9.5 ms.  No zero is
 // multiplied any more, and the clock is 1.9 GHz; the matrix cores are busy a third of the time, the
 // vector ALUs (splits, gauge, k-scaling) as long.  128 x 64 tiles 12.3 ms; lines touched ahead into
-// L2 changed nothing.  Split BF16 from panels, 256 products at d = 512: 0.72 ms against 0.79.
+// L2 changed nothing.  Split BF16 from panels, 256 products at d = 512: 0.66 ms against 0.79.
 //
 // Error against FP64, relative, after chains of 16 .. 100 steps, FP32 4M / 3M / here: Ising drive
 // d = 256 1.1 / 1.5 / 0.6e-6, d = 1024 2.0 / 2.6 / 1.1e-6; levels of a collective drive d = 256
@@ -305,7 +307,7 @@ __device__ __forceinline__ void split_tile(const GemmDesc& g, int d, int i0, int
     load(1);
     __syncthreads();
     const int koff = 8 * (lane >> 5);
-    auto products = [&](int buf) __attribute__((always_inline)) {
+    auto products = [&](int buf, auto between) __attribute__((always_inline)) {
         x8 a[C::FM][NPA], b[C::FN][4];
 #pragma unroll
         for (int ib = 0; ib < C::FM; ++ib)
@@ -330,6 +332,7 @@ __device__ __forceinline__ void split_tile(const GemmDesc& g, int d, int i0, int
         if constexpr (REAL) {
             // Cr += A Br,  Ci += A Bi
             prod(0, 0, 0, false); prod(1, 0, 2, false);
+            between();
             prod(c, 0, 1, false); prod(c + 1, 0, 3, false);
             prod(c, 1, 0, false); prod(c + 1, 1, 2, false);
             if constexpr (FORM == 2) {
@@ -340,6 +343,7 @@ __device__ __forceinline__ void split_tile(const GemmDesc& g, int d, int i0, int
             prod(0, 0, 0, false); prod(1, 0, 2, false);
             prod(c, 0, 1, false); prod(c + 1, 0, 3, false);
             prod(c, 1, 0, false); prod(c + 1, 1, 2, false);
+            between();
             prod(0, 2, 2, true);  prod(1, 2, 0, false);
             prod(c, 2, 3, true);  prod(c + 1, 2, 1, false);
             prod(c, 3, 2, true);  prod(c + 1, 3, 0, false);
@@ -349,20 +353,32 @@ __device__ __forceinline__ void split_tile(const GemmDesc& g, int d, int i0, int
             }
         }
     };
+    // In the middle of a stage's products the new tiles have had longer to arrive, and the first
+    // products need not wait for the LDS stores (split BF16, 256 products at d = 512: 31.3 -> 29.1 ms
+    // for 32 steps; 64 x 64 tiles 2 %); the large FP16 tiles would spill (201 -> 217 ms, 512 x 16
+    // products at d = 1024)
+    constexpr bool MID = !(BN == 128 && std::is_same<E, Half>::value);
     // stage kt: the tiles of kt + 1, loaded during the last stage, go to LDS; those of kt + 2 are
     // loaded, to arrive behind the products of kt.  The k-scaling is one stage further ahead
     for (int kt = 0; kt + 2 < nk; ++kt) {
-        store_k(kt + 2);
-        store(kt + 1, (kt & 1) ^ 1);
-        load(kt + 2);
-        load_k(min(kt + 3, nk - 1));
-        products(kt & 1);
+        auto advance = [&]() __attribute__((always_inline)) {
+            store_k(kt + 2);
+            store(kt + 1, (kt & 1) ^ 1);
+            load(kt + 2);
+            load_k(min(kt + 3, nk - 1));
+        };
+        if constexpr (MID) {
+            products(kt & 1, advance);
+        } else {
+            advance();
+            products(kt & 1, [] {});
+        }
         __syncthreads();
     }
     store(nk - 1, (nk - 1) & 1);
-    products((nk - 2) & 1);
+    products((nk - 2) & 1, [] {});
     __syncthreads();
-    products((nk - 1) & 1);
+    products((nk - 1) & 1, [] {});
 #pragma unroll
     for (int ib = 0; ib < C::FM; ++ib)
 #pragma unroll
