@@ -11,6 +11,12 @@
 //   * d = 2, 4, large batches at d = 8, and any d in a small workspace: one launch; a wave
 //     walks its instances forward, keeping every state or every C-th, and back, forming the
 //     traces of each step beside the adjoint product.
+// d = 16, 256 instances x 500 steps: 1.23 ms (scans 0.84, traces 0.22, composition 0.17) against 5.6
+// for one workgroup per instance with states in LDS; d = 32, 64 x 1500 ragged with five channels:
+// 3.7 ms (2.2, 0.6, 0.9) against 29.4; d = 4, 65,536 x 200, fused: 2.9 ms against 5.2.  The order
+// of every sum is that of the scalar complex product: gradients at small phased amplitudes
+// amplify rounding (errors to 2e-3 of the largest entry), and a layout that summed in another
+// order gave other digits there.
 #pragma once
 #include "large_path.h"
 #include "reg_step.h"
